@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace pic {
 
 // ---------------------------------------------------------------------------------------------
@@ -38,6 +40,7 @@ __device__ __forceinline__ double dpp_r(double v)
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
 
+constexpr int kRowShl1 = 0x101;
 constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
 constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143;
 
@@ -68,31 +71,53 @@ __device__ __forceinline__ R seg_scan(R v, unsigned m)
     return v;
 }
 
-// Segmented inclusive scan of N values at once over the first STEPS DPP steps (STEPS <= 6: the
-// scan spans groups of 2^STEPS lanes).  Step k is applied to every value before step k + 1, so
-// the DPP reads of one value follow the writes of the others and need no wait states.
-template <int STEPS, int N, typename R>
-__device__ __forceinline__ void seg_scan_n(R (&v)[N], unsigned m)
+// Segments of the in-cell deposit: runs of equal keys within groups of 2^STEPS lanes (STEPS <= 4: a group
+// lies in one DPP row).  f[k] is 1 on lanes whose segment reaches 2^k lanes back (no segment starts
+// on the 2^k lanes up to and with this one) and 0 elsewhere, as the factor of step k of the scan; tail
+// marks the last lane of each segment.  Each factor is the one before times its own row-shifted
+// copy; lanes that a shift takes from outside the row read 0, which ends their segments there.
+template <int STEPS>
+__device__ __forceinline__ void seg_factors(int key, float (&f)[STEPS], bool& tail)
 {
-    R t[N];
-#define PIC_SCAN_STEP(K, CTRL, ROWMASK)                                                \
-    if (STEPS > K) {                                                                   \
-        _Pragma("unroll") for (int q = 0; q < N; ++q) t[q] = dpp_r<CTRL, ROWMASK>(v[q]); \
-        _Pragma("unroll") for (int q = 0; q < N; ++q) if (m & (1u << K)) v[q] += t[q];  \
+    static_assert(STEPS >= 1 && STEPS <= 4, "row shifts only");
+    constexpr int G = 1 << STEPS;
+    const int lane = (int)(threadIdx.x & 63);
+    const bool first = lane % G == 0, last = lane % G == G - 1;
+    const int prev = __builtin_amdgcn_update_dpp(0, key, kRowShr1, 0xf, 0xf, true);
+    const int next = __builtin_amdgcn_update_dpp(0, key, kRowShl1, 0xf, 0xf, true);
+    tail = last || next != key;
+    f[0] = first || prev != key ? 0.0f : 1.0f;
+    auto shr = [](float v, auto c) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(c)::value, 0xf, 0xf, true));
+    };
+    if constexpr (STEPS > 1) f[1] = f[0] * shr(f[0], std::integral_constant<int, kRowShr1>{});
+    if constexpr (STEPS > 2) f[2] = f[1] * shr(f[1], std::integral_constant<int, kRowShr2>{});
+    if constexpr (STEPS > 3) f[3] = f[2] * shr(f[2], std::integral_constant<int, kRowShr4>{});
+}
+
+// Segmented inclusive scan of N values at once over the segments of seg_factors: step k adds the value
+// 2^k lanes before times the factor f[k], for every value before step k + 1, so the DPP reads of one
+// value follow the writes of the others and need no wait states.  One fused multiply-add per value and
+// step: v + 1 * t rounds as v + t, v + 0 * t is v (the values are finite).
+template <int STEPS, int N>
+__device__ __forceinline__ void seg_scan_n(double (&v)[N], const float (&f)[STEPS])
+{
+    double t[N];
+#define PIC_SCAN_STEP(K, CTRL)                                                               \
+    if constexpr (STEPS > K) {                                                               \
+        const double fk = (double)f[K];                                                      \
+        _Pragma("unroll") for (int q = 0; q < N; ++q) t[q] = dpp_r<CTRL, 0xf>(v[q]);         \
+        _Pragma("unroll") for (int q = 0; q < N; ++q) v[q] = __builtin_fma(fk, t[q], v[q]);  \
     }
-    PIC_SCAN_STEP(0, kRowShr1, 0xf)
-    PIC_SCAN_STEP(1, kRowShr2, 0xf)
-    PIC_SCAN_STEP(2, kRowShr4, 0xf)
-    PIC_SCAN_STEP(3, kRowShr8, 0xf)
-    PIC_SCAN_STEP(4, kRowBcast15, 0xa)
-    PIC_SCAN_STEP(5, kRowBcast31, 0xc)
+    PIC_SCAN_STEP(0, kRowShr1)
+    PIC_SCAN_STEP(1, kRowShr2)
+    PIC_SCAN_STEP(2, kRowShr4)
+    PIC_SCAN_STEP(3, kRowShr8)
 #undef PIC_SCAN_STEP
 }
 
-// FP32 form of seg_scan_n, on groups of 16 lanes (one DPP row; STEPS <= 4), for the N = 5, 8 and
-// 12 deposit values of 1D, 2D and 3D: each step adds the row-shifted value times a per-lane 0/1
-// factor with one v_fmac_f32 that takes its first operand through DPP (v + 1 * t rounds as v + t;
-// v + 0 * t is v), in place of a shift, an add and a select.  Written as assembly because the
+// FP32 form of seg_scan_n, for the N = 5, 8 and 12 deposit values of 1D, 2D and 3D: each step is one
+// v_fmac_f32 per value that takes its first operand through DPP.  Written as assembly because the
 // compiler does not fold a DPP move into an FMA.  Source lanes outside the row are disabled by the
 // row shift (no bound_ctrl), so those lanes keep v.  A VALU write followed by a DPP read of the same
 // register needs two wait states on this architecture and the compiler cannot see into the asm, so
@@ -131,31 +156,12 @@ __device__ __forceinline__ void fmac_step(float (&v)[N], float f)
 #undef PIC_V12
 
 template <int STEPS, int N>
-__device__ __forceinline__ void seg_scan_n(float (&v)[N], unsigned m)
+__device__ __forceinline__ void seg_scan_n(float (&v)[N], const float (&f)[STEPS])
 {
-    static_assert(STEPS >= 1 && STEPS <= 4, "row shifts only");
-    const float f0 = (m & 1u) ? 1.0f : 0.0f, f1 = (m & 2u) ? 1.0f : 0.0f;
-    const float f2 = (m & 4u) ? 1.0f : 0.0f, f3 = (m & 8u) ? 1.0f : 0.0f;
-    fmac_step<N, 1, STEPS == 1>(v, f0);
-    if constexpr (STEPS > 1) fmac_step<N, 2, STEPS == 2>(v, f1);
-    if constexpr (STEPS > 2) fmac_step<N, 4, STEPS == 3>(v, f2);
-    if constexpr (STEPS > 3) fmac_step<N, 8, true>(v, f3);
-}
-
-// Step masks of seg_masks for the first STEPS steps only.
-template <int STEPS>
-__device__ __forceinline__ unsigned seg_masks_n(bool head)
-{
-    int f = head ? 1 : 0;
-    unsigned m = 0;
-    int fu;
-    if (STEPS > 0) { fu = dpp_i<kRowShr1, 0xf>(f);    if (!f) m |= 1u;  f |= fu; }
-    if (STEPS > 1) { fu = dpp_i<kRowShr2, 0xf>(f);    if (!f) m |= 2u;  f |= fu; }
-    if (STEPS > 2) { fu = dpp_i<kRowShr4, 0xf>(f);    if (!f) m |= 4u;  f |= fu; }
-    if (STEPS > 3) { fu = dpp_i<kRowShr8, 0xf>(f);    if (!f) m |= 8u;  f |= fu; }
-    if (STEPS > 4) { fu = dpp_i<kRowBcast15, 0xa>(f); if (!f) m |= 16u; f |= fu; }
-    if (STEPS > 5) { if (!f) m |= 32u; }
-    return m;
+    fmac_step<N, 1, STEPS == 1>(v, f[0]);
+    if constexpr (STEPS > 1) fmac_step<N, 2, STEPS == 2>(v, f[1]);
+    if constexpr (STEPS > 2) fmac_step<N, 4, STEPS == 3>(v, f[2]);
+    if constexpr (STEPS > 3) fmac_step<N, 8, true>(v, f[3]);
 }
 
 // Plain inclusive scan over the whole wavefront (one segment starting at lane 0).
