@@ -67,7 +67,7 @@ typedef struct {
     int block;          /* threads per particle-kernel workgroup: 64, 128, 256 or 512    */
     int unit;           /* most particles one particle-kernel workgroup takes from a tile */
                         /* (a tile's particles are split into units of at most this many; */
-                        /* 0: one unit per tile; otherwise >= 64)                         */
+                        /* 0: chosen at each sort to fill the device; otherwise >= 64)    */
     int sort_every;     /* cell sort every this many steps (>= 1)                        */
     int series_cap;     /* steps of the current time series kept on the device           */
     int track_continuity; /* 1: measure the continuity residual on every step (slower)   */

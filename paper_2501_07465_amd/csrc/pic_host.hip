@@ -511,19 +511,21 @@ static size_t plan(pic_sim* s, char* base, bool assign)
     h.fdirty = P.take<int>(2 * (size_t)h.nftiles);
     s->max_slots = count_slot_tiles(s);
     h.max_slots = s->max_slots;
-    // units of a tile: ceil(c_t / U) <= c_t / U + 1, so all units <= ceil(N / U) + active tiles
+    // units of a tile: ceil(c_t / U) <= c_t / U + 1, so all units <= ceil(N / U) + active tiles; a cap
+    // chosen at the sort gives at most the goal, or is kUnitMax; it is never below kUnitMin
     long long max_units = s->max_slots;
-    if (h.unit_cap > 0) {
+    {
         long long ntot = 0;
         for (auto& x : s->sp) ntot += x.n;
-        max_units += (ntot + h.unit_cap - 1) / h.unit_cap;
+        if (h.unit_cap > 0) max_units += (ntot + h.unit_cap - 1) / h.unit_cap;
+        else max_units += std::min(std::max<long long>(kUnitGoalMax, ntot / kUnitMax + 1), ntot / kUnitMin + 1);
     }
     h.max_units = (int)std::min<long long>(max_units, 1LL << 30);
     h.tile_slot = P.take<int>(h.ntiles);
     h.tile_nslot = P.take<int>(h.ntiles);
     h.active = P.take<int>(h.ntiles);
     h.n_active = P.take<int>(1);
-    h.units = P.take<int>((size_t)h.max_units * 3);
+    h.units = P.take<UnitDev>((size_t)h.max_units);
     h.n_units = P.take<int>(1);
     h.step_p = P.take<long long>(1);
     h.step_f = P.take<long long>(1);
@@ -695,6 +697,8 @@ static hipError_t launch_load(pic_sim* s, int i)
     return Launchers<double>::load(s->g.dims, s->d, A, s->st);
 }
 
+static Launch make_launch(pic_sim* s);
+
 extern "C" int pic_bind(pic_sim* s, void* dev_arena, size_t bytes, void* hip_stream)
 {
     if (!s) return PIC_EINVAL;
@@ -724,6 +728,12 @@ extern "C" int pic_bind(pic_sim* s, void* dev_arena, size_t bytes, void* hip_str
     // fits it to the blocks its kernel can hold on the device at once
     s->pgrid = std::max(8, (std::min(s->h.max_units, ncu * 8) + 7) / 8 * 8);
     s->ncu = ncu;
+    if (s->h.unit_cap == 0) {
+        const Launch L = make_launch(s);
+        const int b = s->g.precision == PIC_FP32 ? Launchers<float>::particle_blocks(s->g.dims, L)
+                                                 : Launchers<double>::particle_blocks(s->g.dims, L);
+        s->h.unit_goal = std::max(1, std::min(b, kUnitGoalMax));
+    }
     HIPCHK(s, enqueue_fill(s->arena, need - kAlign, s->st));
     if (s->h.einv) {
         // the unit tensor until pic_load_eps_inv: 1.0f, or 1.0 as the words (0, 0x3ff00000)

@@ -64,6 +64,27 @@ constexpr int kPlaneRowsFp64 = 2;
 // wavefronts per SIMD of the 256 CUs)
 constexpr int kFieldTasksMin = 2048;
 
+// Units of a simulation that leaves their size open (unit_cap 0), chosen at each sort from its N
+// particles in A active tiles and the G blocks the particle kernel holds on the device at once.
+//   A < G: at most G units, all in flight at once, as small as that allows: a tile of c particles takes
+//     ceil(c / U) <= c / U + 1 units, so U = N / (G - A) gives at most G of them (but not below
+//     kUnitMin, a chunk of 64 for each of four wavefronts).  Just past G units a few blocks take a
+//     second unit while the rest idle: the 1024^2 disk (16x16 tiles, G = 1024) takes 46 us a step with
+//     about 950 units, 62 with 1100, 75 with whole tiles; the 64^3 sphere (G = 768) 62, 72 and 67.
+//   A >= G: units of at most kUnitMax: every block takes several in any case, and smaller ones even
+//     out the last round (a disk of 9 million particles, 1100 active tiles: 187 us a step, 201 with
+//     whole tiles of 8192) until the window each unit stages and adds costs more than that (the 128^3
+//     sphere: 238 us with 4096, 245 with 2600).
+constexpr int kUnitMin = 256;
+constexpr int kUnitMax = 4096;
+constexpr int kUnitGoalMax = 2048;
+__host__ __device__ inline int auto_unit_cap(long long n, int active, int goal)
+{
+    if (active >= goal) return kUnitMax;
+    const long long u = (n / (goal - active) + 64) / 64 * 64;
+    return (int)(u < kUnitMin ? kUnitMin : (u > 0x7fffffc0LL ? 0x7fffffc0LL : u));
+}
+
 constexpr int kGL = 2;       // low-side halo of the field window (and low reach of a tile's deposits)
 constexpr int kGHf = 2;      // high-side halo of the field window
 constexpr int kGHj = 3;      // high reach of a tile's deposits
@@ -125,6 +146,12 @@ struct SpeciesDev {
     int* vals_alt;
 };
 
+// A work unit of the particle kernel: a tile and the unit's range of each species' (sorted) particles.
+struct UnitDev {
+    int tile;
+    int range[MAXSP][2];
+};
+
 struct SimDev {
     int dims, precision, nspecies, ntiles;
     int n[3], L[3], periodic[3], T[3], Tshift[3], ntile[3];
@@ -144,11 +171,12 @@ struct SimDev {
     int* active;           // [ntiles]: active tile list
     int* n_active;         // device scalar
     int max_slots;         // capacity of the active list (tiles that can hold particles)
-    int* units;            // [max_units][3]: tile, first and end particle in the tile's
-                           // species-concatenated order
+    UnitDev* units;        // [max_units]
     int* n_units;          // device scalar
     int max_units;         // capacity of the unit list
-    int unit_cap;          // most particles per unit (0: one unit per tile)
+    int unit_cap;          // most particles per unit (0: chosen by each sort from unit_goal)
+    int unit_goal;         // the particle kernel's blocks the device holds at once
+    int unit_now;          // the cap of the current unit list
     int* sort_hist;        // radix-sort digit histogram scratch
     int* sort_part;        // radix-sort digit totals [8][256] (copies summed by the row scan)
     double* J[2];          // [words][3][Lvol] J^{n+1/2} by step parity, in quanta (integer-valued
@@ -281,6 +309,8 @@ constexpr int kMaxHistBins = 4096;  // most bins of pic_energy_histogram
 template <typename R>
 struct Launchers {
     static hipError_t particles(int dims, const Launch& L);
+    // blocks of the particle kernel that this launch takes on the device at once
+    static int particle_blocks(int dims, const Launch& L);
     static hipError_t fields(int dims, const Launch& L, int lds_elems);
     // the full-tensor passes of one simulation (its device table entry, its field nodes)
     static hipError_t tensor(int dims, const SimDev* entry, long long lvol, hipStream_t st);

@@ -5,6 +5,8 @@
 // input order (wavefront multisplit with ballots, then waves in order, then blocks in order).
 // All kernels read their arrays through the device SimDev table, so a captured graph stays
 // valid when the array pointers are swapped after each sort.
+#include <algorithm>
+
 #include "pic_dpp.h"
 #include "pic_internal.h"
 #include "pic_sort.h"
@@ -277,8 +279,8 @@ __global__ void k_tile_ranges(SimDev* __restrict__ S, int s, int passes, int swa
 }
 
 // Active tiles (any species has particles) and their work units: a tile holding c particles (all
-// species) gets ceil(c / U) units of at most U particles, in its species-concatenated order (one
-// unit when U is 0); the units of a tile take consecutive slots.
+// species) gets ceil(c / U) units of at most U particles, in its species-concatenated order, U the
+// caller's cap or one chosen here (auto_unit_cap); the units of a tile take consecutive slots.
 //
 // Tiles are listed in blocks of kUnitBlock tiles along each active axis (x fastest inside a block,
 // blocks in x-fastest order), so that tiles near each other along every axis are near each other
@@ -339,16 +341,65 @@ __device__ __forceinline__ int compact_count(const SimDev* S, int t)
     for (int s = 0; s < S->nspecies; ++s) c += S->sp[s].tile_start[t + 1] - S->sp[s].tile_start[t];
     return c;
 }
-__device__ __forceinline__ int compact_units(const SimDev* S, int c)
+// the cap of the list's units: the caller's, or chosen for its active tiles
+__device__ __forceinline__ int compact_cap(const SimDev* S, int active)
 {
-    return c == 0 ? 0 : (S->unit_cap > 0 ? (c + S->unit_cap - 1) / S->unit_cap : 1);
+    if (S->unit_cap > 0) return S->unit_cap;
+    long long n = 0;
+    for (int s = 0; s < S->nspecies; ++s) n += S->sp[s].n;
+    return auto_unit_cap(n, active, S->unit_goal);
+}
+__device__ __forceinline__ int compact_units(int c, int cap) { return (int)(((long long)c + cap - 1) / cap); }
+
+// the k units of tile t (c particles), at slots p .. p + k - 1 of the unit list: equal parts of its
+// species-concatenated order, in whole chunks of 64 where the cap allows
+__device__ __forceinline__ void put_units(SimDev* S, int p, int k, int t, int c, int cap)
+{
+    int per = (c + k - 1) / k;
+    per = (per + 63) / 64 * 64;
+    per = min(per, cap);  // k = ceil(c / cap), so no part is empty
+    const int ns = S->nspecies;
+    int t0[MAXSP], n[MAXSP];
+#pragma unroll
+    for (int s = 0; s < MAXSP; ++s) {
+        t0[s] = s < ns ? S->sp[s].tile_start[t] : 0;
+        n[s] = s < ns ? S->sp[s].tile_start[t + 1] - t0[s] : 0;
+    }
+    for (int q = 0; q < k; ++q) {
+        UnitDev& u = S->units[p + q];
+        u.tile = t;
+        const int ub = q * per, ue = min(c, (q + 1) * per);
+        int base = 0;  // first index of species s in the concatenated order
+#pragma unroll
+        for (int s = 0; s < MAXSP; ++s) {
+            u.range[s][0] = t0[s] + min(max(ub - base, 0), n[s]);
+            u.range[s][1] = t0[s] + min(max(ue - base, 0), n[s]);
+            base += n[s];
+        }
+    }
 }
 
-__global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restrict__ S)
+// Active tiles per block (sort_hist, free once the species are sorted), where the cap is chosen from
+// their number.
+__global__ void __launch_bounds__(kScanThreads) k_compact_active(SimDev* __restrict__ S)
+{
+    __shared__ int wsum[kScanThreads / 64];
+    int ca = 0;
+    for (int t = blockIdx.x * kScanThreads + threadIdx.x; t < S->ntiles; t += gridDim.x * kScanThreads)
+        ca += compact_count(S, t) > 0 ? 1 : 0;
+    int ta;
+    block_scan(ca, wsum, &ta);
+    if (threadIdx.x == 0) S->sort_hist[blockIdx.x] = ta;
+}
+
+__global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restrict__ S, int nactive)
 {
     __shared__ int wsum[kScanThreads / 64];
     const CompactGeom G(S);
     int ca = 0, cu = 0;
+    int active = 0;
+    if (nactive > 0) block_scan((int)threadIdx.x < nactive ? S->sort_hist[threadIdx.x] : 0, wsum, &active);
+    const int cap = compact_cap(S, active);
     const int r0 = blockIdx.x * G.rpb, r1 = min(G.rounds, r0 + G.rpb);
     for (int round = r0; round < r1; ++round) {
         int t[kCompactK];
@@ -357,7 +408,7 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restri
         for (int j = 0; j < kCompactK; ++j) {
             const int c = t[j] >= 0 ? compact_count(S, t[j]) : 0;
             ca += c > 0 ? 1 : 0;
-            cu += compact_units(S, c);
+            cu += compact_units(c, cap);
         }
     }
     int ta, tu;
@@ -366,6 +417,7 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restri
     if (threadIdx.x == 0) {
         S->sort_part[2 * blockIdx.x] = ta;
         S->sort_part[2 * blockIdx.x + 1] = tu;
+        if (blockIdx.x == 0) S->unit_now = cap;
     }
 }
 
@@ -410,7 +462,6 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
 {
     __shared__ int wsum[kScanThreads / 64];
     const CompactGeom G(S);
-    const int U = S->unit_cap;
     int c[kCompactK], tt[kCompactK];
     int ra = 0, ru = 0;
     G.tiles_of(S, threadIdx.x * kCompactK, tt);
@@ -418,10 +469,12 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
     for (int j = 0; j < kCompactK; ++j) {
         c[j] = tt[j] >= 0 ? compact_count(S, tt[j]) : 0;
         ra += c[j] > 0 ? 1 : 0;
-        ru += compact_units(S, c[j]);
     }
     int ta, tu;
     int pa = block_scan(ra, wsum, &ta) - ra;
+    const int cap = compact_cap(S, ta);
+#pragma unroll
+    for (int j = 0; j < kCompactK; ++j) ru += compact_units(c[j], cap);
     int pu = block_scan(ru, wsum, &tu) - ru;
     const bool fits = ta <= S->max_slots && tu <= S->max_units;
 #pragma unroll
@@ -429,16 +482,11 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
         const int t = tt[j];
         if (t < 0) continue;
         if (c[j] > 0 && fits) {
-            const int k = compact_units(S, c[j]);
+            const int k = compact_units(c[j], cap);
             S->active[pa] = t;
             S->tile_slot[t] = pu;
             S->tile_nslot[t] = k;
-            for (int q = 0; q < k; ++q) {
-                int* u = S->units + 3 * (pu + q);
-                u[0] = t;
-                u[1] = U > 0 ? q * U : 0;
-                u[2] = U > 0 ? min(c[j], (q + 1) * U) : c[j];
-            }
+            put_units(S, pu, k, t, c[j], cap);
             ++pa;
             pu += k;
         } else {
@@ -449,6 +497,7 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
     if (threadIdx.x == 0) {
         *S->n_active = fits ? ta : 0;
         *S->n_units = fits ? tu : 0;
+        S->unit_now = cap;
         if (!fits) atomicAdd(S->over_count, 1ull << 40);
     }
 }
@@ -457,7 +506,7 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_place(SimDev* __restri
 {
     __shared__ int wsum[kScanThreads / 64];
     const CompactGeom G(S);
-    const int U = S->unit_cap;
+    const int cap = S->unit_now;
     const bool fits = S->sort_part[kPartCopies * kRadix - 1] != 0;
     int oa = S->sort_part[2 * blockIdx.x], ou = S->sort_part[2 * blockIdx.x + 1];  // the blocks before
     const int r0 = blockIdx.x * G.rpb, r1 = min(G.rounds, r0 + G.rpb);
@@ -469,7 +518,7 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_place(SimDev* __restri
         for (int j = 0; j < kCompactK; ++j) {
             c[j] = tt[j] >= 0 ? compact_count(S, tt[j]) : 0;
             ra += c[j] > 0 ? 1 : 0;
-            ru += compact_units(S, c[j]);
+            ru += compact_units(c[j], cap);
         }
         int sa, su;
         int pa = block_scan(ra, wsum, &sa) - ra + oa;
@@ -479,16 +528,11 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_place(SimDev* __restri
             const int t = tt[j];
             if (t < 0) continue;
             if (c[j] > 0 && fits) {
-                const int k = compact_units(S, c[j]);
+                const int k = compact_units(c[j], cap);
                 S->active[pa] = t;
                 S->tile_slot[t] = pu;
                 S->tile_nslot[t] = k;
-                for (int q = 0; q < k; ++q) {
-                    int* u = S->units + 3 * (pu + q);
-                    u[0] = t;
-                    u[1] = U > 0 ? q * U : 0;
-                    u[2] = U > 0 ? min(c[j], (q + 1) * U) : c[j];
-                }
+                put_units(S, pu, k, t, c[j], cap);
                 ++pa;
                 pu += k;
             } else {
@@ -553,7 +597,13 @@ hipError_t enqueue_compact(SimDev* dS, const SimDev& h, hipStream_t st)
         return hipGetLastError();
     }
     const int nb = (int)(rounds < kCompactBlocks ? rounds : kCompactBlocks);
-    hipLaunchKernelGGL(k_compact_count, dim3(nb), dim3(kScanThreads), 0, st, dS);
+    // (a block per 16384 tiles, within the scratch of the smallest sort, 256 counts)
+    int na = 0;
+    if (h.unit_cap == 0) {
+        na = std::min(256, (h.ntiles + 16 * kScanThreads - 1) / (16 * kScanThreads));
+        hipLaunchKernelGGL(k_compact_active, dim3(na), dim3(kScanThreads), 0, st, dS);
+    }
+    hipLaunchKernelGGL(k_compact_count, dim3(nb), dim3(kScanThreads), 0, st, dS, na);
     hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(kScanThreads), 0, st, dS, nb);
     hipLaunchKernelGGL(k_compact_place, dim3(nb), dim3(kScanThreads), 0, st, dS);
     return hipGetLastError();
