@@ -219,12 +219,18 @@ static int setup_grid(pic_sim* s)
         if (g.dims == 3 && a == 1 && g.precision == PIC_FP64) h.FT[a] = kPlaneRowsFp64;
         // the 3D plane march takes row groups over all L_y rows (the last group shifted down to end
         // at the last row), columns and plane chunks over the cells (the last one also owns node n).
-        // On a small grid the plane chunks are shortened until there are enough tasks to keep
-        // several wavefronts per SIMD (each task's march is a chain of dependent plane loads), down
-        // to two planes (one on grids of fewer than 32768 cells).
-        if (g.dims == 3 && a == 2)
-            while (h.FT[2] > ((long long)g.n[0] * g.n[1] * g.n[2] < 32768 ? 1 : 2) && (long long)h.nft[0] * h.nft[1] * ((g.n[2] + h.FT[2] - 1) / h.FT[2]) < kFieldTasksMin)
-                h.FT[2] /= 2;
+        // The plane chunk, at most FieldTile<3>::Z, is the one with the shortest march: rounds of resident
+        // wavefronts times the planes of a chunk and its prologue (see kFieldWaves).
+        if (g.dims == 3 && a == 2) {
+            const long long strips = (long long)h.nft[0] * h.nft[1];
+            const int waves = g.precision == PIC_FP32 && !g.eps_cells ? 3 * kFieldWaves : 2 * kFieldWaves;
+            double best = 0.0;
+            for (int z = ft[2][2]; z >= 1; --z) {
+                const long long tasks = strips * ((g.n[2] + z - 1) / z);
+                const double cost = (double)((tasks + waves - 1) / waves) * (z + kFieldPrologue);
+                if (z == ft[2][2] || cost < best) { best = cost; h.FT[2] = z; }
+            }
+        }
         const int span = (g.dims == 3 && a == 1) ? h.L[a] : g.n[a];
         h.nft[a] = (span + h.FT[a] - 1) / h.FT[a];
         h.nftiles *= h.nft[a];
@@ -509,6 +515,7 @@ static size_t plan(pic_sim* s, char* base, bool assign)
     const size_t jw = s->g.precision == PIC_FP64 ? JWords<double>::n : JWords<float>::n;
     for (int p = 0; p < 2; ++p) h.J[p] = P.take<double>(jw * 3 * L);
     h.fdirty = P.take<int>(2 * (size_t)h.nftiles);
+    h.fmask = P.take<unsigned>((size_t)h.nftiles);
     s->max_slots = count_slot_tiles(s);
     h.max_slots = s->max_slots;
     // units of a tile: ceil(c_t / U) <= c_t / U + 1, so all units <= ceil(N / U) + active tiles; a cap

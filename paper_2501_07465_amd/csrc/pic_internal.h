@@ -60,9 +60,14 @@ constexpr int kUnitQueueWords = 2 * kXcds;
 // rows of a plane-march task in the FP64 form (its slabs of doubles take twice the registers: with
 // three rows it held one wavefront per SIMD)
 constexpr int kPlaneRowsFp64 = 2;
-// fewest plane-march tasks a grid is split into before its plane chunks are shortened (about two
-// wavefronts per SIMD of the 256 CUs)
-constexpr int kFieldTasksMin = 2048;
+// The plane march takes its tasks in rounds of the wavefronts the device holds, 256 CUs x 4 SIMDs times
+// the wavefronts per SIMD that the kernel's registers allow (3 in the plain FP32 form, else 2), and a
+// task's time follows its planes plus a prologue worth about kFieldPrologue of them (its first loads and
+// its flags).  The rounds decide more than the planes read twice: the 256^3 grid takes 0.346 ms with
+// chunks of 10 planes (3.6 rounds) and 0.360 with 9 (4.1), the FP64 96^3 one 66 us with 2 planes (2.3
+// rounds) and 51 with 5 (0.96).
+constexpr int kFieldWaves = 1024;
+constexpr double kFieldPrologue = 1.5;
 
 // Units of a simulation that leaves their size open (unit_cap 0), chosen at each sort from its N
 // particles in A active tiles and the G blocks the particle kernel holds on the device at once.
@@ -185,6 +190,7 @@ struct SimDev {
                            // atomics, deposits outside the windows add directly
     double jq, jq_inv;     // quanta per unit of current density, and its inverse (powers of two)
     int* fdirty;           // [2][nftiles] where the owned nodes of J[p] hold deposits: 1D tiles 0/1; 2D, 3D tasks a bit per particle-tile column (~0: all)
+    unsigned* fmask;       // [nftiles] particle-tile columns (bits; 1D: 0/1) whose deposits reach a field task
     long long* over_stamp; // [2] step+1 of the last overflow per parity
     unsigned long long* over_count;
     int* nonfinite;        // set to 1 by the particle kernel when a pushed velocity is not finite
@@ -272,6 +278,14 @@ inline size_t particle_lds_bytes(bool fp64, int vf, int vj, int block)
     size_t f = es * (6 * (size_t)vf + (size_t)kStrayScratch * (size_t)(block / 64));
     f = (f + 7) / 8 * 8;
     return f + 8 * (size_t)(fp64 ? JWords<double>::n : JWords<float>::n) * 3 * (size_t)vj;
+}
+
+// Particle tiles whose deposits reach [x0, x1] along an axis (cells, unwrapped): lo .. lo + count - 1, those
+// tt with tt T - kGL <= x <= tt T + T - 1 + kGHj.
+__host__ __device__ inline void reaching_tiles(int x0, int x1, int T, int sh, int& lo, int& count)
+{
+    lo = -((-(x0 - T + 1 - kGHj)) >> sh);
+    count = ((x1 + kGL) >> sh) - lo + 1;
 }
 
 // ---- launchers (defined in the kernel translation units) ---------------------------------------

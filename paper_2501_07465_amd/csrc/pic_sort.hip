@@ -545,6 +545,61 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_place(SimDev* __restri
     }
 }
 
+// fmask of every field task: the columns (x index) of active particle tiles whose deposits reach it, as bits
+// from the first reaching column on; one bit for all of them where there are more than 32 (tiles
+// narrower than 3 cells), and in 1D.  A task reaches one cell past its own along each axis (the last
+// one along an open axis also owns node n).  The active tiles change only with the sort, so the field
+// kernel reads the mask and does not search the tiles itself: its search of up to 150 of them was 2 of
+// the 13 us of the 16^3 cube's field kernel.  One wavefront per task, one candidate tile per lane.
+template <int DIM>
+__global__ void __launch_bounds__(256) k_field_masks(SimDev* __restrict__ Sd)
+{
+    const SimDev& S = *Sd;
+    const int lane = threadIdx.x & 63;
+    const int ft = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (ft >= S.nftiles) return;
+    const int tf[3] = {ft % S.nft[0], (ft / S.nft[0]) % S.nft[1], ft / (S.nft[0] * S.nft[1])};
+    int tlo[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
+    for (int a = 0; a < DIM; ++a) {
+        int x0 = tf[a] * S.FT[a], x1 = x0 + S.FT[a];
+        if (DIM == 3 && a == 1) {
+            // the plane march's row groups end at the last row
+            x0 = max(0, min(x0, S.L[1] - S.FT[1]));
+            x1 = x0 + S.FT[1];
+        }
+        if (DIM == 3 && a == 2 && tf[2] == S.nft[2] - 1) x1 = S.L[2];
+        reaching_tiles(x0, x1, S.T[a], S.Tshift[a], tlo[a], cnt[a]);
+    }
+    unsigned xm = 0u;
+    for (int t = lane; t < cnt[0] * cnt[1] * cnt[2]; t += 64) {
+        int t3[3] = {tlo[0] + t % cnt[0], tlo[1] + (t / cnt[0]) % cnt[1], tlo[2] + t / (cnt[0] * cnt[1])};
+        bool in = true;
+        for (int a = 0; a < DIM; ++a) {
+            if (S.periodic[a]) {
+                t3[a] %= S.ntile[a];
+                if (t3[a] < 0) t3[a] += S.ntile[a];
+            } else if (t3[a] < 0 || t3[a] >= S.ntile[a]) {
+                in = false;
+            }
+        }
+        if (in && S.tile_slot[(t3[2] * S.ntile[1] + t3[1]) * S.ntile[0] + t3[0]] >= 0)
+            xm |= DIM > 1 && cnt[0] <= 32 ? 1u << (t % cnt[0]) : ~0u;
+    }
+    for (int off = 32; off > 0; off >>= 1) xm |= (unsigned)__shfl_xor((int)xm, off, 64);
+    if (lane == 0) S.fmask[ft] = xm;
+}
+
+static hipError_t enqueue_field_masks(SimDev* dS, const SimDev& h, hipStream_t st)
+{
+    const dim3 grid((h.nftiles + 3) / 4), block(256);
+    switch (h.dims) {
+    case 1: hipLaunchKernelGGL(k_field_masks<1>, grid, block, 0, st, dS); break;
+    case 2: hipLaunchKernelGGL(k_field_masks<2>, grid, block, 0, st, dS); break;
+    default: hipLaunchKernelGGL(k_field_masks<3>, grid, block, 0, st, dS); break;
+    }
+    return hipGetLastError();
+}
+
 // --------------------------------------------------------------------------------------------
 hipError_t enqueue_sort(SimDev* dS, int s, int n, int passes, int elem, hipStream_t st)
 {
@@ -594,7 +649,7 @@ hipError_t enqueue_compact(SimDev* dS, const SimDev& h, hipStream_t st)
     const long long rounds = (nt + kCompactK * kScanThreads - 1) / (kCompactK * kScanThreads);
     if (rounds <= 1) {
         hipLaunchKernelGGL(k_compact_one, dim3(1), dim3(kScanThreads), 0, st, dS);
-        return hipGetLastError();
+        return enqueue_field_masks(dS, h, st);
     }
     const int nb = (int)(rounds < kCompactBlocks ? rounds : kCompactBlocks);
     // (a block per 16384 tiles, within the scratch of the smallest sort, 256 counts)
@@ -606,7 +661,7 @@ hipError_t enqueue_compact(SimDev* dS, const SimDev& h, hipStream_t st)
     hipLaunchKernelGGL(k_compact_count, dim3(nb), dim3(kScanThreads), 0, st, dS, na);
     hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(kScanThreads), 0, st, dS, nb);
     hipLaunchKernelGGL(k_compact_place, dim3(nb), dim3(kScanThreads), 0, st, dS);
-    return hipGetLastError();
+    return enqueue_field_masks(dS, h, st);
 }
 
 }  // namespace pic
