@@ -708,22 +708,35 @@ hipError_t enqueue_sum(const double* x, long long n, double* part, int nb, hipSt
     return hipGetLastError();
 }
 
-// out[v] = reduction over b of part[b * nv + v] in block order (op 0 sum, 1 max); one thread per v
-__global__ void k_final(const double* __restrict__ part, int nb, int nv, int op, double* out)
+// out[v] = reduction over b of part[b * nv + v] (op 0 sum, 1 max), in a fixed order: each thread its
+// strided entries, then a tree (one thread in turn took 88 us for 1024 partials, most of a reading of
+// an energy)
+__global__ void __launch_bounds__(256) k_final(const double* __restrict__ part, int nb, int nv, int op, double* out)
 {
-    const int v = threadIdx.x;
-    if (v >= nv) return;
-    double acc = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        const double x = part[b * nv + v];
-        acc = op ? fmax(acc, x) : acc + x;
+    __shared__ double sh[256];
+    for (int v = 0; v < nv; ++v) {
+        double acc = 0.0;
+        for (int b = threadIdx.x; b < nb; b += 256) {
+            const double x = part[b * nv + v];
+            acc = op ? fmax(acc, x) : acc + x;
+        }
+        sh[threadIdx.x] = acc;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) {
+                const double x = sh[threadIdx.x + w];
+                sh[threadIdx.x] = op ? fmax(sh[threadIdx.x], x) : sh[threadIdx.x] + x;
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) out[v] = sh[0];
+        __syncthreads();
     }
-    out[v] = acc;
 }
 
 hipError_t enqueue_final(const double* part, int nb, int nv, int op, double* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(64), 0, st, part, nb, nv, op, out);
+    hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, st, part, nb, nv, op, out);
     return hipGetLastError();
 }
 
