@@ -2,8 +2,6 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 namespace pic {
 
 // ---------------------------------------------------------------------------------------------
@@ -13,10 +11,13 @@ namespace pic {
 // The per-step "add" predicates depend only on the segment heads, so they are computed once and
 // reused for every value.
 // ---------------------------------------------------------------------------------------------
+// Lanes whose source lies outside the row (or the wavefront) read 0, as do the rows that ROWMASK leaves
+// out.  With every row enabled that is the instruction's own bound control: no register has to hold
+// the 0, and the move folds into the instruction that uses it.
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ int dpp_i(int v)
 {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWMASK, 0xf, false);
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWMASK, 0xf, ROWMASK == 0xf);
 }
 
 template <int CTRL, int ROWMASK>
@@ -83,16 +84,12 @@ __device__ __forceinline__ void seg_factors(int key, float (&f)[STEPS], bool& ta
     constexpr int G = 1 << STEPS;
     const int lane = (int)(threadIdx.x & 63);
     const bool first = lane % G == 0, last = lane % G == G - 1;
-    const int prev = __builtin_amdgcn_update_dpp(0, key, kRowShr1, 0xf, 0xf, true);
-    const int next = __builtin_amdgcn_update_dpp(0, key, kRowShl1, 0xf, 0xf, true);
+    const int prev = dpp_i<kRowShr1, 0xf>(key), next = dpp_i<kRowShl1, 0xf>(key);
     tail = last || next != key;
     f[0] = first || prev != key ? 0.0f : 1.0f;
-    auto shr = [](float v, auto c) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(c)::value, 0xf, 0xf, true));
-    };
-    if constexpr (STEPS > 1) f[1] = f[0] * shr(f[0], std::integral_constant<int, kRowShr1>{});
-    if constexpr (STEPS > 2) f[2] = f[1] * shr(f[1], std::integral_constant<int, kRowShr2>{});
-    if constexpr (STEPS > 3) f[3] = f[2] * shr(f[2], std::integral_constant<int, kRowShr4>{});
+    if constexpr (STEPS > 1) f[1] = f[0] * dpp_r<kRowShr1, 0xf>(f[0]);
+    if constexpr (STEPS > 2) f[2] = f[1] * dpp_r<kRowShr2, 0xf>(f[1]);
+    if constexpr (STEPS > 3) f[3] = f[2] * dpp_r<kRowShr4, 0xf>(f[2]);
 }
 
 // Segmented inclusive scan of N values at once over the segments of seg_factors: step k adds the value
