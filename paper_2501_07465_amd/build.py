@@ -30,6 +30,7 @@ UNITS = {
     "pic_k64.hip": ["-ffp-contract=off"],
     "pic_sort.hip": [],
     "pic_host.hip": [],
+    "pic_readback.hip": [],
 }
 DEPS = ["pic_internal.h", "pic_sort.h", "pic_kernels.inc"]
 

@@ -15,6 +15,7 @@
 
 #include "pic.h"
 #include "pic_internal.h"
+#include "pic_readback.h"
 #include "pic_sort.h"
 
 using namespace pic;
@@ -301,6 +302,7 @@ extern "C" int pic_create(const pic_grid_desc* g, pic_sim** out)
         delete s;
         return r;
     }
+    readback_retain();
     g_create_err.clear();
     *out = s;
     return PIC_OK;
@@ -1262,21 +1264,64 @@ extern "C" int pic_sync(pic_sim* s)
 // ---------------------------------------------------------------------------------------------
 // Diagnostics
 // ---------------------------------------------------------------------------------------------
-template <typename R>
-static void from_real(const std::vector<char>& buf, size_t n, double* dst, size_t stride)
+// a device array of the simulation's reals as one job that writes it to dst as doubles
+static ReadbackJob reals_to(const pic_sim* s, const void* src, size_t n, double* dst)
 {
-    const R* p = reinterpret_cast<const R*>(buf.data());
-    for (size_t i = 0; i < n; ++i) dst[i * stride] = double(p[i]);
+    ReadbackJob j;
+    j.src = {{src, (size_t)s->es}};
+    j.n = n;
+    const bool f32 = s->es == 4;
+    j.put = [dst, f32](const char* const* a, size_t first, size_t count) {
+        double* d = dst + first;
+        if (f32) {
+            const float* p = reinterpret_cast<const float*>(a[0]);
+            for (size_t i = 0; i < count; ++i) d[i] = double(p[i]);
+        } else {
+            memcpy(d, a[0], count * sizeof(double));
+        }
+    };
+    return j;
 }
 
-static int fetch_real(pic_sim* s, const void* src, size_t n, double* dst, size_t stride)
+// positions [n][3], velocities [n][3] and displacements [n][3] of species sid
+template <typename R>
+static ReadbackJob particles_to(const pic_sim* s, int sid, double* out)
 {
-    std::vector<char> buf(n * s->es);
-    if (n) {
-        HIPCHK(s, hipMemcpyAsync(buf.data(), src, buf.size(), hipMemcpyDeviceToHost, s->st));
-        HIPCHK(s, hipStreamSynchronize(s->st));
-    }
-    if (s->es == 4) from_real<float>(buf, n, dst, stride); else from_real<double>(buf, n, dst, stride);
+    const SpeciesHost& x = s->sp[sid];
+    const size_t n = (size_t)x.n;
+    const int p = x.parity, dims = s->g.dims;
+    const bool bound = x.d.kind == PIC_BOUND, dm = x.d.kind == PIC_DIRAC && x.d.mass_per_particle;
+    ReadbackJob j;
+    j.n = n;
+    j.src.push_back({x.cell[p], sizeof(int)});
+    for (int a = 0; a < dims; ++a) j.src.push_back({x.off[p][a], sizeof(R)});
+    for (int a = 0; a < 3; ++a) j.src.push_back({x.v[p][a], sizeof(R)});
+    for (int a = 0; a < (bound ? 3 : (dm ? 1 : 0)); ++a) j.src.push_back({x.xi[p][a], sizeof(R)});
+    const double q = x.d.q;
+    j.put = [s, out, n, dims, bound, dm, q](const char* const* arr, size_t first, size_t count) {
+        double* X = out + 3 * first;
+        double* V = out + 3 * n + 3 * first;
+        double* XI = out + 6 * n + 3 * first;
+        const int* cell = reinterpret_cast<const int*>(arr[0]);
+        for (size_t i = 0; i < count; ++i) {
+            int c[3];
+            unpack_cell(s->h, cell[i], c);
+            for (int a = 0; a < 3; ++a) {
+                X[3 * i + a] = a < dims ? ((double)c[a] + (double)reinterpret_cast<const R*>(arr[1 + a])[i]) * s->g.dx[a] : 0.0;
+                V[3 * i + a] = (double)reinterpret_cast<const R*>(arr[1 + dims + a])[i];
+                XI[3 * i + a] = bound ? (double)reinterpret_cast<const R*>(arr[4 + dims + a])[i] : 0.0;
+            }
+            if (dm) XI[3 * i] = q / (double)reinterpret_cast<const R*>(arr[4 + dims])[i];  // stored q / m_d -> m_d
+        }
+    };
+    return j;
+}
+
+static int run_readback(pic_sim* s, const std::vector<ReadbackJob>& jobs)
+{
+    const hipError_t e = readback(jobs, s->st);
+    if (e == hipErrorOutOfMemory) return fail(s, PIC_ENOMEM, "export: out of host memory");
+    HIPCHK(s, e);
     return PIC_OK;
 }
 
@@ -1361,9 +1406,8 @@ extern "C" int pic_energy_histogram_static(pic_sim* s, int sid, double e_max, in
     return PIC_OK;
 }
 
-extern "C" int pic_diag(pic_sim* s, int kind, int arg, double* out, size_t cap, size_t* n_out)
+static int diag(pic_sim* s, int kind, int arg, double* out, size_t cap, size_t* n_out)
 {
-    if (!s) return PIC_EINVAL;
     if (!s->bound) return fail(s, PIC_ESTATE, "bind first");
     HIPCHK(s, hipStreamSynchronize(s->st));
     const bool f32 = s->g.precision == PIC_FP32;
@@ -1441,64 +1485,44 @@ extern "C" int pic_diag(pic_sim* s, int kind, int arg, double* out, size_t cap, 
         out[0] = (double)f;
         return PIC_OK;
     }
-    case PIC_DIAG_EXPORT_PARTICLES: {
-        SpeciesHost& x = s->sp[arg];
-        const size_t n = (size_t)x.n;
-        const int p = x.parity;
-        std::vector<int> cell(n);
-        if (n) {
-            HIPCHK(s, hipMemcpyAsync(cell.data(), x.cell[p], n * sizeof(int), hipMemcpyDeviceToHost, s->st));
-            HIPCHK(s, hipStreamSynchronize(s->st));
-        }
-        double* X = out;
-        double* V = out + 3 * n;
-        double* XI = out + 6 * n;
-        std::fill(out, out + 9 * n, 0.0);
-        int r;
-        for (int a = 0; a < 3; ++a) {
-            if (a < s->g.dims && (r = fetch_real(s, x.off[p][a], n, X + a, 3))) return r;
-            if ((r = fetch_real(s, x.v[p][a], n, V + a, 3))) return r;
-            if (x.d.kind == PIC_BOUND && (r = fetch_real(s, x.xi[p][a], n, XI + a, 3))) return r;
-        }
-        if (x.d.kind == PIC_DIRAC && x.d.mass_per_particle) {
-            if ((r = fetch_real(s, x.xi[p][0], n, XI, 3))) return r;
-            for (size_t i = 0; i < n; ++i) XI[3 * i] = x.d.q / XI[3 * i];  // stored q / m_d -> m_d
-        }
-        for (size_t i = 0; i < n; ++i) {
-            int c[3];
-            unpack_cell(s->h, cell[i], c);
-            for (int a = 0; a < 3; ++a)
-                X[3 * i + a] = a < s->g.dims ? ((double)c[a] + X[3 * i + a]) * s->g.dx[a] : 0.0;
-        }
-        return PIC_OK;
-    }
+    case PIC_DIAG_EXPORT_PARTICLES:
+        return run_readback(s, {s->es == 4 ? particles_to<float>(s, arg, out) : particles_to<double>(s, arg, out)});
     case PIC_DIAG_EXPORT_FIELDS: {
-        int r;
-        for (int c = 0; c < 3; ++c) {
-            if ((r = fetch_real(s, s->h.E[par][c], L, out + c * L, 1))) return r;
-            if ((r = fetch_real(s, s->h.B[par][c], L, out + (3 + c) * L, 1))) return r;
-        }
-        return PIC_OK;
+        std::vector<ReadbackJob> jobs;
+        for (int c = 0; c < 3; ++c) jobs.push_back(reals_to(s, s->h.E[par][c], L, out + c * L));
+        for (int c = 0; c < 3; ++c) jobs.push_back(reals_to(s, s->h.B[par][c], L, out + (3 + c) * L));
+        return run_readback(s, jobs);
     }
     case PIC_DIAG_EXPORT_CURRENT: {
-        int r;
+        std::vector<ReadbackJob> jobs;
         for (int c = 0; c < 3; ++c)
-            if ((r = fetch_real(s, static_cast<char*>(s->h.jtrack) + c * L * s->es, L, out + c * L, 1))) return r;
-        return PIC_OK;
+            jobs.push_back(reals_to(s, static_cast<char*>(s->h.jtrack) + c * L * s->es, L, out + c * L));
+        return run_readback(s, jobs);
     }
     case PIC_DIAG_KEYS: {
         const size_t n = (size_t)s->sp[arg].n;
-        std::vector<int> k(n);
         HIPCHK(s, enqueue_keys_only(dtab(s), arg, (int)n, s->st));
-        if (n) {
-            HIPCHK(s, hipMemcpyAsync(k.data(), s->h.sp[arg].keys, n * sizeof(int), hipMemcpyDeviceToHost, s->st));
-            HIPCHK(s, hipStreamSynchronize(s->st));
-        }
-        for (size_t i = 0; i < n; ++i) out[i] = (double)k[i];
-        return PIC_OK;
+        ReadbackJob j;
+        j.src = {{s->h.sp[arg].keys, sizeof(int)}};
+        j.n = n;
+        j.put = [out](const char* const* a, size_t first, size_t count) {
+            const int* k = reinterpret_cast<const int*>(a[0]);
+            for (size_t i = 0; i < count; ++i) out[first + i] = (double)k[i];
+        };
+        return run_readback(s, {j});
     }
     }
     return PIC_EINVAL;
+}
+
+extern "C" int pic_diag(pic_sim* s, int kind, int arg, double* out, size_t cap, size_t* n_out)
+{
+    if (!s) return PIC_EINVAL;
+    try {
+        return diag(s, kind, arg, out, cap, n_out);
+    } catch (const std::exception&) {
+        return PIC_ENOMEM;  // (no text: that would allocate)
+    }
 }
 
 extern "C" const char* pic_last_error(const pic_sim* s)
@@ -1530,6 +1554,7 @@ extern "C" void pic_destroy(pic_sim* s)
     if (s->batch_refs && s->owner) (void)pic_batch_remove(s->owner, s);
     drop_graph(s);
     delete s;
+    readback_release();
 }
 
 // ---------------------------------------------------------------------------------------------
