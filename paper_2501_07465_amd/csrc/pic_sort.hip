@@ -341,13 +341,16 @@ __device__ __forceinline__ int compact_count(const SimDev* S, int t)
     for (int s = 0; s < S->nspecies; ++s) c += S->sp[s].tile_start[t + 1] - S->sp[s].tile_start[t];
     return c;
 }
+__device__ __forceinline__ long long compact_total(const SimDev* S)
+{
+    long long n = 0;
+    for (int s = 0; s < S->nspecies; ++s) n += S->sp[s].n;
+    return n;
+}
 // the cap of the list's units: the caller's, or chosen for its active tiles
 __device__ __forceinline__ int compact_cap(const SimDev* S, int active)
 {
-    if (S->unit_cap > 0) return S->unit_cap;
-    long long n = 0;
-    for (int s = 0; s < S->nspecies; ++s) n += S->sp[s].n;
-    return auto_unit_cap(n, active, S->unit_goal);
+    return S->unit_cap > 0 ? S->unit_cap : auto_unit_cap(compact_total(S), active, S->unit_goal);
 }
 __device__ __forceinline__ int compact_units(int c, int cap) { return (int)(((long long)c + cap - 1) / cap); }
 
@@ -472,7 +475,21 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
     }
     int ta, tu;
     int pa = block_scan(ra, wsum, &ta) - ra;
-    const int cap = compact_cap(S, ta);
+    int cap = compact_cap(S, ta);
+    if (S->unit_cap == 0 && ta > 0 && ta < S->unit_goal) {
+        // the bound behind the chosen cap counts a part unit for every tile; the tiles are at hand here, so
+        // the smallest cap (in chunks) that keeps to the goal is searched for between N / goal and it
+        int lo = max(kUnitMin, (int)min((compact_total(S) / S->unit_goal + 64) / 64 * 64, (long long)cap));
+        while (lo < cap) {
+            const int mid = (lo + (cap - lo) / 2) / 64 * 64;
+            int u = 0, tot;
+#pragma unroll
+            for (int j = 0; j < kCompactK; ++j) u += compact_units(c[j], mid);
+            block_scan(u, wsum, &tot);
+            if (tot <= S->unit_goal) cap = mid;
+            else lo = mid + 64;
+        }
+    }
 #pragma unroll
     for (int j = 0; j < kCompactK; ++j) ru += compact_units(c[j], cap);
     int pu = block_scan(ru, wsum, &tu) - ru;
