@@ -565,6 +565,11 @@ static size_t plan(pic_sim* s, char* base, bool assign)
     h.sort_hist = P.take<int>((size_t)256 * nb);
     h.sort_part = P.take<int>(8 * 256);
     h.nspecies = (int)s->sp.size();
+    {
+        long long n = 0;
+        for (auto& x : s->sp) n += x.n;
+        h.n_chunks = (int)((n + 63) / 64);
+    }
     for (size_t i = 0; i < s->sp.size(); ++i) {
         SpeciesHost& x = s->sp[i];
         SpeciesDev& d = h.sp[i];
@@ -1624,7 +1629,7 @@ static SimDev idle_entry(const pic_batch* b)
     e.dims = b->dims;
     e.precision = b->precision;
     long long* w = reinterpret_cast<long long*>(b->idle);
-    e.n_units = reinterpret_cast<int*>(w);  // no units
+    e.n_units = e.n_active = reinterpret_cast<int*>(w);  // no units, no tiles
     e.step_p = w + 1;
     e.step_f = w + 2;
     return e;

@@ -72,22 +72,32 @@ constexpr double kFieldPrologue = 1.5;
 // Units of a simulation that leaves their size open (unit_cap 0), chosen at each sort from its N
 // particles in A active tiles and the G blocks the particle kernel holds on the device at once.
 //   A < G: at most G units, all in flight at once, as small as that allows: a tile of c particles takes
-//     ceil(c / U) <= c / U + 1 units, so U = N / (G - A) gives at most G of them (but not below
-//     kUnitMin, a chunk of 64 for each of four wavefronts).  Just past G units a few blocks take a
-//     second unit while the rest idle: the 1024^2 disk (16x16 tiles, G = 1024) takes 46 us a step with
-//     about 950 units, 62 with 1100, 75 with whole tiles; the 64^3 sphere (G = 768) 62, 72 and 67.
+//     ceil(c / U) <= c / U + 1 units, so U = N / (G - A) gives at most G of them.  Just past G units a
+//     few blocks take a second unit while the rest idle: the 1024^2 disk (16x16 tiles, G = 1024) takes
+//     46 us a step with about 950 units, 62 with 1100, 75 with whole tiles; the 64^3 sphere (G = 768) 62,
+//     72 and 67.  U is not below unit_floor: 1024 particles, where a smaller unit gains a few percent for
+//     a simulation on its own (a disk of 227 thousand: 29 us a step with 512, 30 with 1024) but costs a
+//     batch, whose blocks all have work in any case (16 serving requests: 803 us a step with units of 256
+//     and up, 540 to 560 with 1024 to whole tiles); less only where 64 units would not be made (a slab
+//     of 16 thousand: 18 us with 256, 23 with 1024).
 //   A >= G: units of at most kUnitMax: every block takes several in any case, and smaller ones even
 //     out the last round (a disk of 9 million particles, 1100 active tiles: 187 us a step, 201 with
 //     whole tiles of 8192) until the window each unit stages and adds costs more than that (the 128^3
 //     sphere: 238 us with 4096, 245 with 2600).
-constexpr int kUnitMin = 256;
+constexpr int kUnitMin = 256;  // (a chunk of 64 for each of four wavefronts)
 constexpr int kUnitMax = 4096;
 constexpr int kUnitGoalMax = 2048;
+__host__ __device__ inline int unit_floor(long long n)
+{
+    const long long u = (n / 64 + 63) / 64 * 64;
+    return (int)(u < kUnitMin ? kUnitMin : (u > 1024 ? 1024 : u));
+}
 __host__ __device__ inline int auto_unit_cap(long long n, int active, int goal)
 {
     if (active >= goal) return kUnitMax;
     const long long u = (n / (goal - active) + 64) / 64 * 64;
-    return (int)(u < kUnitMin ? kUnitMin : (u > 0x7fffffc0LL ? 0x7fffffc0LL : u));
+    const int least = unit_floor(n);
+    return (int)(u < least ? least : (u > 0x7fffffc0LL ? 0x7fffffc0LL : u));
 }
 
 constexpr int kGL = 2;       // low-side halo of the field window (and low reach of a tile's deposits)
@@ -159,6 +169,7 @@ struct UnitDev {
 
 struct SimDev {
     int dims, precision, nspecies, ntiles;
+    int n_chunks;          // particles of all species, in chunks of 64
     int n[3], L[3], periodic[3], T[3], Tshift[3], ntile[3];
     int Wf[3], Wj[3];      // particle-window extents (1 on inactive axes)
     int gl[3];             // low halo per axis (kGL on active axes, 0 otherwise)

@@ -479,7 +479,7 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
     if (S->unit_cap == 0 && ta > 0 && ta < S->unit_goal) {
         // the bound behind the chosen cap counts a part unit for every tile; the tiles are at hand here, so
         // the smallest cap (in chunks) that keeps to the goal is searched for between N / goal and it
-        int lo = max(kUnitMin, (int)min((compact_total(S) / S->unit_goal + 64) / 64 * 64, (long long)cap));
+        int lo = max(unit_floor(compact_total(S)), (int)min((compact_total(S) / S->unit_goal + 64) / 64 * 64, (long long)cap));
         while (lo < cap) {
             const int mid = (lo + (cap - lo) / 2) / 64 * 64;
             int u = 0, tot;

@@ -43,3 +43,42 @@ def test_chosen_units_match_stated_units(label, n, tile, block):
         err = np.abs(got[k] - ref[k]).max() / scale
         print(f"  {k}: {err:.2e}", flush=True)
         assert err <= 1e-12, k
+
+
+@pytest.mark.parametrize("members,unit", [(9, 64), (5, 0), (3, 512)])
+def test_runs_of_units_in_a_batch_match_runs_alone(members, unit):
+    """A batch's blocks take runs of units (9 members in units of 64: several units a run, runs that end
+    inside a tile and cross from member to member) from ranges equal in work (members of very different
+    size): every member is bit for bit the run of its own."""
+    from paper_2501_07465_amd import pic
+    steps = 40
+    ws = []
+    for i in range(members):
+        w = W.small("disk2d")
+        w["n"], w["tile"] = [136, 72, 1], [32, 16, 1]
+        w["species"][0]["ppc"] = w["species"][1]["ppc"] = (4, 30, 90)[i % 3]
+        w["seed"] = 100 + i
+        ws.append(w)
+
+    def export(sim):
+        out = list(sim.fields())
+        for s in sim.species:
+            out += list(sim.particles(s))
+        return out + [sim.current_series()]
+
+    kw = dict(precision="fp32", block=256, unit=unit, series_cap=steps + 8)
+    alone = []
+    for w in ws:
+        sim = pic.Simulation(copy.deepcopy(w), **kw)
+        sim.step(steps)
+        alone.append(export(sim))
+    batch = pic.Batch(members, 2, "fp32")
+    sims = [pic.Simulation(copy.deepcopy(w), stream=batch.stream, **kw) for w in ws]
+    for sim in sims:
+        batch.add(sim)
+    batch.step(steps)
+    batch.stream.synchronize()
+    for i, sim in enumerate(sims):
+        print(f"member {i}", flush=True)
+        for a, b in zip(alone[i], export(sim)):
+            assert np.array_equal(a, b)
