@@ -66,6 +66,7 @@ struct pic_sim {
     unsigned* pqueue = nullptr;  // the particle kernel's unit queue (in the arena, zeroed at bind)
     int field_lds = 0;
     int max_slots = 0;
+    long long max_ftiles = 0;  // field tasks of one row (plane) each
     bool graphs = false;
     hipGraphExec_t gexec = nullptr;
     std::vector<int> graph_species;  // species sorted inside the captured period
@@ -136,6 +137,32 @@ static double dirac_mass(double ef, double vf) { return (ef / vf) / (2.0 * vf); 
 // ---------------------------------------------------------------------------------------------
 // Grid validation and derived geometry
 // ---------------------------------------------------------------------------------------------
+// The field tasks of a simulation stepped with sims - 1 others: the 3D plane march takes row groups over
+// all L_y rows (the last group shifted down to end at the last row), columns and plane chunks over the
+// cells (the last one also owns node n); the 2D row sweep columns and row groups over the cells.
+// Returns the most tasks any chunk gives (one row or plane each).
+static long long set_field_tiles(const pic_grid_desc& g, SimDev& h, int sims)
+{
+    const int ft[3][3] = {{FieldTile<1>::X, FieldTile<1>::Y, FieldTile<1>::Z},
+                          {FieldTile<2>::X, FieldTile<2>::Y, FieldTile<2>::Z},
+                          {FieldTile<3>::X, FieldTile<3>::Y, FieldTile<3>::Z}};
+    const bool fp64 = g.precision == PIC_FP64;
+    long long strips = 1, most = 1;
+    for (int a = 0; a < 3; ++a) {
+        h.FT[a] = a < g.dims ? ft[g.dims - 1][a] : 1;
+        if (g.dims == 3 && a == 1 && fp64) h.FT[a] = kPlaneRowsFp64;
+        if (g.dims > 1 && a == g.dims - 1) {
+            h.FT[a] = field_chunk(strips * sims, g.n[a], h.FT[a], kFieldWaves * field_waves(g.dims, fp64, g.eps_cells != 0));
+            most = strips * g.n[a];
+        }
+        const int span = (g.dims == 3 && a == 1) ? h.L[a] : g.n[a];
+        h.nft[a] = (span + h.FT[a] - 1) / h.FT[a];
+        strips *= h.nft[a];
+    }
+    h.nftiles = (int)strips;
+    return std::max(most, strips);
+}
+
 static int setup_grid(pic_sim* s)
 {
     pic_grid_desc& g = s->g;
@@ -208,35 +235,9 @@ static int setup_grid(pic_sim* s)
     h.Vj = h.Wj[0] * h.Wj[1] * h.Wj[2];
     const size_t plds = particle_lds_bytes(g.precision == PIC_FP64, h.Vf, h.Vj, g.block);
     if (plds > 65536) return fail(s, PIC_EINVAL, "particle tile needs %zu bytes of LDS (> 64 KiB)", plds);
-    // field tiles
-    const int ft[3][3] = {{FieldTile<1>::X, FieldTile<1>::Y, FieldTile<1>::Z},
-                          {FieldTile<2>::X, FieldTile<2>::Y, FieldTile<2>::Z},
-                          {FieldTile<3>::X, FieldTile<3>::Y, FieldTile<3>::Z}};
     h.Lvol = 1;
-    h.nftiles = 1;
-    for (int a = 0; a < 3; ++a) {
-        h.FT[a] = a < g.dims ? ft[g.dims - 1][a] : 1;
-        if (g.dims == 2 && a == 1 && g.eps_cells) h.FT[a] = kSweepRowsEps;
-        if (g.dims == 3 && a == 1 && g.precision == PIC_FP64) h.FT[a] = kPlaneRowsFp64;
-        // the 3D plane march takes row groups over all L_y rows (the last group shifted down to end
-        // at the last row), columns and plane chunks over the cells (the last one also owns node n).
-        // The plane chunk, at most FieldTile<3>::Z, is the one with the shortest march: rounds of resident
-        // wavefronts times the planes of a chunk and its prologue (see kFieldWaves).
-        if (g.dims == 3 && a == 2) {
-            const long long strips = (long long)h.nft[0] * h.nft[1];
-            const int waves = g.precision == PIC_FP32 && !g.eps_cells ? 3 * kFieldWaves : 2 * kFieldWaves;
-            double best = 0.0;
-            for (int z = ft[2][2]; z >= 1; --z) {
-                const long long tasks = strips * ((g.n[2] + z - 1) / z);
-                const double cost = (double)((tasks + waves - 1) / waves) * (z + kFieldPrologue);
-                if (z == ft[2][2] || cost < best) { best = cost; h.FT[2] = z; }
-            }
-        }
-        const int span = (g.dims == 3 && a == 1) ? h.L[a] : g.n[a];
-        h.nft[a] = (span + h.FT[a] - 1) / h.FT[a];
-        h.nftiles *= h.nft[a];
-        h.Lvol *= h.L[a];
-    }
+    for (int a = 0; a < 3; ++a) h.Lvol *= h.L[a];
+    s->max_ftiles = set_field_tiles(g, h, 1);
     // the full tensor's node lists hold int32 node indices
     if (g.eps_cells == 2 && h.Lvol > 0x7fffffffLL)
         return fail(s, PIC_EINVAL, "a full dielectric tensor needs fewer than 2^31 field nodes");
@@ -516,8 +517,8 @@ static size_t plan(pic_sim* s, char* base, bool assign)
     }
     const size_t jw = s->g.precision == PIC_FP64 ? JWords<double>::n : JWords<float>::n;
     for (int p = 0; p < 2; ++p) h.J[p] = P.take<double>(jw * 3 * L);
-    h.fdirty = P.take<int>(2 * (size_t)h.nftiles);
-    h.fmask = P.take<unsigned>((size_t)h.nftiles);
+    h.fdirty = P.take<int>(2 * (size_t)s->max_ftiles);
+    h.fmask = P.take<unsigned>((size_t)s->max_ftiles);
     s->max_slots = count_slot_tiles(s);
     h.max_slots = s->max_slots;
     // units of a tile: ceil(c_t / U) <= c_t / U + 1, so all units <= ceil(N / U) + active tiles; a cap
@@ -1717,6 +1718,17 @@ static bool graph_covers(const pic_batch* b, const pic_sim* s)
            (!has_extra(s) || b->g_ext) && !s->h.eoff;
 }
 
+// The member's field tasks for a batch of sims slots (1: on its own again), before its table entry is
+// written: where they change, the marks of the tasks that hold deposits mean other tasks, so all are marked
+// (each is cleared once more), and the masks are found by the sort that its next step begins with.
+static hipError_t retile_fields(pic_sim* s, int sims, hipStream_t st)
+{
+    const int before = s->h.nftiles;
+    set_field_tiles(s->g, s->h, sims);
+    if (s->h.nftiles == before) return hipSuccess;
+    return enqueue_fill_pattern(s->h.fdirty, 2 * sizeof(int) * (size_t)s->h.nftiles, ~0u, ~0u, st);
+}
+
 extern "C" int pic_batch_add(pic_batch* b, pic_sim* s)
 {
     if (!b || !s) return PIC_EINVAL;
@@ -1736,13 +1748,18 @@ extern "C" int pic_batch_add(pic_batch* b, pic_sim* s)
     }
     SimDev* entry = b->table + i;
     for (size_t j = 0; j < s->sp.size(); ++j) mirror_species(s, (int)j);
-    if (put_entry(entry, s->h, b->st) != hipSuccess) return bfail(b, PIC_EDEVICE, "table entry write failed");
+    const auto undo = [&](const char* msg) {
+        (void)retile_fields(s, 1, b->st);
+        return bfail(b, PIC_EDEVICE, msg);
+    };
+    if (retile_fields(s, b->max_sims, b->st) != hipSuccess || put_entry(entry, s->h, b->st) != hipSuccess)
+        return undo("table entry write failed");
     // the member's periodic sorts, captured against its slot's entry (the host parities are put back:
     // each launch of the graph flips them)
     std::vector<int> par, sorted;
     for (auto& x : s->sp) par.push_back(x.parity);
     if (hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal) != hipSuccess)
-        return bfail(b, PIC_EDEVICE, "sort capture failed");
+        return undo("sort capture failed");
     SimDev* own = s->d;
     s->d = entry;
     const int r = enqueue_sort_all(s, &sorted);
@@ -1755,7 +1772,7 @@ extern "C" int pic_batch_add(pic_batch* b, pic_sim* s)
     if (graph) (void)hipGraphDestroy(graph);
     if (r || e != hipSuccess) {
         (void)put_entry(entry, idle_entry(b), b->st);
-        return bfail(b, PIC_EDEVICE, r ? s->err.c_str() : hipGetErrorString(e));
+        return undo(r ? s->err.c_str() : hipGetErrorString(e));
     }
     s->bsort = gx;
     s->graph_species = sorted;
@@ -1788,9 +1805,11 @@ extern "C" int pic_batch_remove(pic_batch* b, pic_sim* s)
     s->d_batch = nullptr;
     s->bslot = -1;
     s->owner = nullptr;
-    // the member's own table from the host state (pointer parities), after its last batched step
+    // the member's own table from the host state (pointer parities), after its last batched step; its field
+    // tasks are again those of a simulation on its own, whose next step begins with a sort
     for (size_t j = 0; j < s->sp.size(); ++j) mirror_species(s, (int)j);
-    if (put_entry(s->d, s->h, s->st) != hipSuccess) return bfail(b, PIC_EDEVICE, "table entry write failed");
+    if (retile_fields(s, 1, s->st) != hipSuccess || put_entry(s->d, s->h, s->st) != hipSuccess)
+        return bfail(b, PIC_EDEVICE, "table entry write failed");
     batch_reap(b, false);
     return PIC_OK;
 }
@@ -1815,6 +1834,7 @@ extern "C" void pic_batch_destroy(pic_batch* b)
         s->d_batch = nullptr;
         s->bslot = -1;
         s->owner = nullptr;
+        (void)retile_fields(s, 1, s->st);
         for (size_t j = 0; j < s->sp.size(); ++j) mirror_species(s, (int)j);
         (void)put_entry(s->d, s->h, s->st);
     }

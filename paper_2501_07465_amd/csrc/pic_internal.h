@@ -45,12 +45,9 @@ struct FieldTile;
 template <>
 struct FieldTile<1> { static constexpr int X = 256, Y = 1, Z = 1; };
 template <>
-struct FieldTile<2> { static constexpr int X = 61, Y = 5, Z = 1; };  // row-sweep task: 61 columns of a wavefront, 5 rows
-// rows of a row-sweep task in a simulation with a per-cell permittivity (its kernel keeps a deeper
-// load ring and is faster on taller tasks)
-constexpr int kSweepRowsEps = 6;
+struct FieldTile<2> { static constexpr int X = 61, Y = 6, Z = 1; };  // row-sweep task: 61 columns of a wavefront, at most 6 rows
 template <>
-struct FieldTile<3> { static constexpr int X = 61, Y = 3, Z = 10; };  // plane-march task: 61 columns, 3 rows, 10 planes
+struct FieldTile<3> { static constexpr int X = 61, Y = 3, Z = 10; };  // plane-march task: 61 columns, 3 rows, at most 10 planes
 // XCDs of the MI355X: workgroups are dispatched to them round-robin
 constexpr int kXcds = 8;
 // device words of a particle-kernel unit queue: a next-unit counter and a finished-block counter
@@ -60,14 +57,35 @@ constexpr int kUnitQueueWords = 2 * kXcds;
 // rows of a plane-march task in the FP64 form (its slabs of doubles take twice the registers: with
 // three rows it held one wavefront per SIMD)
 constexpr int kPlaneRowsFp64 = 2;
-// The plane march takes its tasks in rounds of the wavefronts the device holds, 256 CUs x 4 SIMDs times
-// the wavefronts per SIMD that the kernel's registers allow (3 in the plain FP32 form, else 2), and a
-// task's time follows its planes plus a prologue worth about kFieldPrologue of them (its first loads and
-// its flags).  The rounds decide more than the planes read twice: the 256^3 grid takes 0.346 ms with
-// chunks of 10 planes (3.6 rounds) and 0.360 with 9 (4.1), the FP64 96^3 one 66 us with 2 planes (2.3
-// rounds) and 51 with 5 (0.96).
+// The row sweep and the plane march take their tasks in rounds of the wavefronts the device holds, 256 CUs x 4
+// SIMDs times the wavefronts per SIMD that the kernel's registers allow (in the plain FP32 row sweep 4: the
+// fifth gains nothing), and a task's time follows its rows (planes) plus a prologue worth about
+// kFieldPrologue of them (its first loads and its flags).  So the rows (planes) of a task are those with the
+// shortest rounds x (rows + prologue), the most of them where that is equal.  The rounds decide more
+// than the rows read twice: the 256^3 grid takes 0.346 ms with chunks of 10 planes (3.6 rounds) and
+// 0.360 with 9 (4.1), the FP64 96^3 one 66 us with 2 planes (2.3 rounds) and 51 with 5 (0.96).  Row sweeps
+// of 1, 2, 3, 5 rows: 300^2 9.1, 9.4, 10.5, 12.5 us; 600^2 14.4, 11.3, 11.8, 13.8; 1024^2 25.7, 19.8, 20.0,
+// 18.7; FP64 500^2 17.9, 14.4, 15.0, 16.5.  The members of a batch share the rounds, so a member's tasks are
+// counted once per slot: 16 requests take 622 us a step with 1 row and 564 with 5.
 constexpr int kFieldWaves = 1024;
 constexpr double kFieldPrologue = 1.5;
+// wavefronts of a SIMD that the field kernel's tasks are rounded by
+constexpr int field_waves(int dims, bool fp64, bool eps)
+{
+    return dims == 2 ? (fp64 ? (eps ? 2 : 3) : 4) : (fp64 || eps ? 2 : 3);
+}
+// rows (planes) of a field task over n of them in each of strips columns of tasks, at most most
+inline int field_chunk(long long strips, int n, int most, int waves)
+{
+    int chunk = most;
+    double best = 0.0;
+    for (int z = most; z >= 1; --z) {
+        const long long tasks = strips * ((n + z - 1) / z);
+        const double cost = (double)((tasks + waves - 1) / waves) * (z + kFieldPrologue);
+        if (z == most || cost < best) { best = cost; chunk = z; }
+    }
+    return chunk;
+}
 
 // Units of a simulation that leaves their size open (unit_cap 0), chosen at each sort from its N
 // particles in A active tiles and the G blocks the particle kernel holds on the device at once.
