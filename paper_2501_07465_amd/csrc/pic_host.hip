@@ -60,7 +60,6 @@ struct pic_sim {
     bool need_sort = true;
     std::string err;
     int es = 4;              // element size of reals
-    int passes = 1;
     int pgrid = 1;
     int ncu = 0;                 // compute units of the device at pic_bind
     unsigned* pqueue = nullptr;  // the particle kernel's unit queue (in the arena, zeroed at bind)
@@ -230,7 +229,8 @@ static int setup_grid(pic_sim* s)
     h.ntiles = (int)tiles;
     int bits = 1;
     while ((1LL << bits) < keyspace) ++bits;
-    s->passes = (bits + 7) / 8;
+    h.sort_passes = (bits + kDigitBits - 1) / kDigitBits;
+    h.sort_bits = (bits + h.sort_passes - 1) / h.sort_passes;
     h.Vf = h.Wf[0] * h.Wf[1] * h.Wf[2];
     h.Vj = h.Wj[0] * h.Wj[1] * h.Wj[2];
     const size_t plds = particle_lds_bytes(g.precision == PIC_FP64, h.Vf, h.Vj, g.block);
@@ -531,9 +531,6 @@ static size_t plan(pic_sim* s, char* base, bool assign)
         else max_units += std::min(std::max<long long>(kUnitGoalMax, ntot / kUnitMax + 1), ntot / kUnitMin + 1);
     }
     h.max_units = (int)std::min<long long>(max_units, 1LL << 30);
-    h.tile_slot = P.take<int>(h.ntiles);
-    h.tile_nslot = P.take<int>(h.ntiles);
-    h.active = P.take<int>(h.ntiles);
     h.n_active = P.take<int>(1);
     h.units = P.take<UnitDev>((size_t)h.max_units);
     h.n_units = P.take<int>(1);
@@ -561,10 +558,11 @@ static size_t plan(pic_sim* s, char* base, bool assign)
     s->part = P.take<double>(kDiagBlocks * 4);
     s->outv = P.take<double>(16);
     s->cont = P.take<double>(2);
-    long long nb = 1;
-    for (auto& x : s->sp) nb = std::max(nb, (x.n + sort_ipb(x.n) - 1) / sort_ipb(x.n));
-    h.sort_hist = P.take<int>((size_t)256 * nb);
-    h.sort_part = P.take<int>(8 * 256);
+    int nb = 1;
+    for (auto& x : s->sp) nb = std::max(nb, sort_blocks((int)x.n, sort_shift((int)x.n)));
+    h.sort_hist = P.take<int>(std::max<size_t>(256, (size_t)nb << h.sort_bits));
+    h.sort_part = P.take<int>(kSortPart);
+    h.compact_part = P.take<int>(kCompactPart);
     h.nspecies = (int)s->sp.size();
     {
         long long n = 0;
@@ -1034,18 +1032,24 @@ extern "C" int pic_init_fields(pic_sim* s, int mode)
 // ---------------------------------------------------------------------------------------------
 static int enqueue_sort_all(pic_sim* s, std::vector<int>* sorted)
 {
+    int swap = 0;
     for (size_t i = 0; i < s->sp.size(); ++i) {
         SpeciesHost& x = s->sp[i];
         if (x.d.kind == PIC_BOUND && x.sorted_once) continue;  // anchors never move
+        SortShape q;
+        q.cover(s->h, (int)x.n);
+        q.elem = s->es;
+        HIPCHK(s, enqueue_sort(s->d, 1, (int)i, false, q, s->st));
         if (x.n > 0) {
-            HIPCHK(s, enqueue_sort(s->d, (int)i, (int)x.n, s->passes, s->es, s->st));
             x.parity ^= 1;
+            swap |= 1 << i;
         }
-        HIPCHK(s, enqueue_ranges(s->d, (int)i, s->h.ntiles, s->passes, x.n > 0, s->st));
         x.sorted_once = true;
         if (sorted) sorted->push_back((int)i);
     }
-    HIPCHK(s, enqueue_compact(s->d, s->h, s->st));
+    CompactShape q;
+    q.cover(s->h);
+    HIPCHK(s, enqueue_compact(s->d, 1, q, swap, s->st));
     s->need_sort = false;
     return PIC_OK;
 }

@@ -200,10 +200,7 @@ struct SimDev {
     // fields, planar [comp][z][y][x], R; two buffers: step n reads [n & 1] and writes [(n+1) & 1]
     void* E[2][3];
     void* B[2][3];
-    int* tile_slot;        // [ntiles]: first unit of an active tile, -1 otherwise
-    int* tile_nslot;       // [ntiles]: units of an active tile (consecutive)
-    int* active;           // [ntiles]: active tile list
-    int* n_active;         // device scalar
+    int* n_active;         // device scalar: tiles that hold particles
     int max_slots;         // capacity of the active list (tiles that can hold particles)
     UnitDev* units;        // [max_units]
     int* n_units;          // device scalar
@@ -212,7 +209,9 @@ struct SimDev {
     int unit_goal;         // the particle kernel's blocks the device holds at once
     int unit_now;          // the cap of the current unit list
     int* sort_hist;        // radix-sort digit histogram scratch
-    int* sort_part;        // radix-sort digit totals [8][256] (copies summed by the row scan)
+    int* sort_part;        // radix-sort digit totals (copies summed by the row scan; zero between passes)
+    int* compact_part;     // block totals of the unit list
+    int sort_passes, sort_bits;  // radix passes over the key's bits, bits of each
     double* J[2];          // [words][3][Lvol] J^{n+1/2} by step parity, in quanta (integer-valued
                            // FP64; FP32 form one word, FP64 form two: quanta and their fraction in
                            // units of 2^-kJqLoBits): every tile's current window is added by exact

@@ -15,67 +15,85 @@
 
 namespace pic {
 
-constexpr int kRadixBits = 8;
-constexpr int kRadix = 1 << kRadixBits;
+constexpr int kRadixMax = 1 << kDigitBits;
 constexpr int kSortBlock = 1024;
 // the fused digit totals are spread over kPartCopies copies (block b adds into copy b % copies) so
 // that fewer blocks queue on each address; the row scan sums the copies
 constexpr int kPartCopies = 8;
+static_assert(kPartCopies * kRadixMax == kSortPart, "scratch of the digit totals");
+static_assert(kRadixMax <= kSortBlock, "a thread of the scatter per digit");
+// Which species a launch sorts: species s, or of each of the table's slots (grid.y) its s-th moving one.
+struct SortSel {
+    int s, moving;
+};
 
-// keys[i] = tile-major key of particle i's cell (anchor cell for bound particles).  The values the
-// passes carry start as the identity, which the first scatter pass forms from the index (not stored).
-// Block 0 also clears the digit totals the first histogram pass adds into.
+// the species that sel names in the slot's entry, or -1
+__device__ __forceinline__ int sel_species(const SimDev& S, const SortSel& sel)
+{
+    if (!sel.moving) return sel.s;
+    int j = sel.s;
+    for (int s = 0; s < S.nspecies; ++s)
+        if (S.sp[s].kind != BOUND && S.sp[s].n > 0 && j-- == 0) return s;
+    return -1;
+}
+
+// keys[i] = tile-major key of particle i's cell (anchor cell for bound particles)
+__device__ __forceinline__ int particle_key(const SimDev& S, const SpeciesDev& sp, int i)
+{
+    int c[3];
+    unpack_cell(S, sp.cell[i], c);
+    return cell_key(S, c);
+}
+
 __global__ void k_keys(SimDev* __restrict__ S, int s)
 {
     const SpeciesDev& sp = S->sp[s];
-    const int n = sp.n;
-    if (blockIdx.x == 0)
-        for (int d = threadIdx.x; d < kPartCopies * kRadix; d += blockDim.x) S->sort_part[d] = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        int c[3];
-        unpack_cell(*S, sp.cell[i], c);
-        sp.keys[i] = cell_key(*S, c);
-    }
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < sp.n; i += gridDim.x * blockDim.x) sp.keys[i] = particle_key(*S, sp, i);
 }
 
-// digit histogram per block: hist[d * nb + b].  For sorts of at most kFuseBlocks blocks the digit
-// totals part[d] are summed here with one atomic per block and digit (part is zero on entry: cleared
-// by k_keys, then by each scatter pass); larger sorts form them in k_radix_rowsum.
-constexpr int kFuseBlocks = 1024;
-
-__global__ void __launch_bounds__(kSortBlock) k_radix_hist(SimDev* __restrict__ S, int s, int pass, int ipb, int fuse)
+// digit histogram per block: hist[b * nd + d], each block's row written and read whole.  The first pass forms the keys from the cells (the values that
+// the passes carry start as the identity, which its scatter forms from the index).
+template <bool FIRST>
+__global__ void __launch_bounds__(kSortBlock) k_radix_hist(const SimDev* __restrict__ sims, SortSel sel, int pass)
 {
-    __shared__ int h[kRadix];
-    const SpeciesDev& sp = S->sp[s];
-    const int* keys = (pass & 1) ? sp.keys_alt : sp.keys;
-    const int n = sp.n;
-    const int nb = (n + ipb - 1) / ipb;
-    for (int i = threadIdx.x; i < kRadix; i += blockDim.x) h[i] = 0;
-    __syncthreads();
-    const int b = blockIdx.x;
-    if (b < nb) {
+    __shared__ int h[kRadixMax];
+    const SimDev& S = sims[blockIdx.y];
+    const int s = sel_species(S, sel);
+    if (s < 0 || pass >= S.sort_passes) return;
+    const SpeciesDev& sp = S.sp[s];
+    int* keys = (pass & 1) ? sp.keys_alt : sp.keys;
+    const int n = sp.n, sh = sort_shift(n), ipb = 1 << sh, nb = sort_blocks(n, sh);
+    const int nd = 1 << S.sort_bits, shift = pass * S.sort_bits;
+    const bool fuse = nb <= kFuseBlocks && nb > kDirectBlocks;
+    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+        for (int d = threadIdx.x; d < nd; d += kSortBlock) h[d] = 0;
+        __syncthreads();
         const int lo = b * ipb, hi = min(n, lo + ipb);
-        const int shift = pass * kRadixBits;
-        for (int i = lo + threadIdx.x; i < hi; i += blockDim.x) atomicAdd(&h[(keys[i] >> shift) & (kRadix - 1)], 1);
-    }
-    __syncthreads();
-    if (b < nb)
-        for (int d = threadIdx.x; d < kRadix; d += blockDim.x) {
-            S->sort_hist[d * nb + b] = h[d];
-            if (fuse && h[d]) atomicAdd(&S->sort_part[(b % kPartCopies) * kRadix + d], h[d]);
+        for (int i = lo + threadIdx.x; i < hi; i += kSortBlock) {
+            int key;
+            if constexpr (FIRST) sp.keys[i] = key = particle_key(S, sp, i);
+            else key = keys[i];
+            atomicAdd(&h[(key >> shift) & (nd - 1)], 1);
         }
+        __syncthreads();
+        for (int d = threadIdx.x; d < nd; d += kSortBlock) {
+            const int c = h[d];
+            S.sort_hist[b * nd + d] = c;
+            if (fuse && c) atomicAdd(&S.sort_part[(b % kPartCopies) * kRadixMax + d], c);
+        }
+        __syncthreads();
+    }
 }
 
-// Exclusive scan of hist[0 .. kRadix * nb) (digit-major), one block per digit: each row scanned with
-// its offset, the sum of the totals of the lower digits (the totals come from the histogram pass).
 constexpr int kScanThreads = 1024;
 constexpr int kUnitBlock = 4;  // tiles per active axis of a block of the unit list
 
-// inclusive scan of v over the block (kScanThreads threads): DPP wavefront scans, then the wave
-// totals in order; *total receives the block total
+// inclusive scan of v over a block of NT threads: DPP wavefront scans, then the wave totals in order;
+// *total receives the block total
+template <int NT = kScanThreads>
 __device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
 {
-    constexpr int NW = kScanThreads / 64;
+    constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int inc = seg_scan<int>(v, scan_masks(lane));
     if (lane == 63) wsum[wave] = inc;
@@ -91,90 +109,159 @@ __device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
     return carry + inc;
 }
 
-// part[d] = sum over blocks b of hist[d * nb + b] (sorts of many blocks: the histogram pass's
-// per-digit atomics would queue on 256 addresses)
-__global__ void __launch_bounds__(kScanThreads) k_radix_rowsum(SimDev* __restrict__ S, int s, int ipb)
+// Digits of a block of the row scan (64 bytes of each row of hist), and the groups of rows it takes them in.
+constexpr int kScanDigits = 16;
+constexpr int kScanGroups = kScanThreads / kScanDigits;
+constexpr int kScanKeep = 8;  // rows of a group held in registers between its two passes (up to 512 blocks)
+
+// part[d] = sum over blocks b of hist[b * nd + d] (sorts of many blocks: the histogram pass's
+// per-digit atomics would queue on the digits' addresses)
+__global__ void __launch_bounds__(kScanThreads) k_radix_rowsum(const SimDev* __restrict__ sims, SortSel sel, int pass)
 {
-    __shared__ int wsum[kScanThreads / 64];
-    const int n = S->sp[s].n;
-    const int nb = (n + ipb - 1) / ipb;
-    const int* row = S->sort_hist + (long long)blockIdx.x * nb;
-    int acc = 0;
-    for (int b = threadIdx.x; b < nb; b += kScanThreads) acc += row[b];
-    int total;
-    block_scan(acc, wsum, &total);
-    if (threadIdx.x == 0) S->sort_part[blockIdx.x] = total;  // copy 0; the other copies stay zero
+    __shared__ int part[kScanGroups][kScanDigits];
+    const SimDev& S = sims[blockIdx.y];
+    const int s = sel_species(S, sel);
+    if (s < 0 || pass >= S.sort_passes) return;
+    const int n = S.sp[s].n, nb = sort_blocks(n, sort_shift(n)), nd = 1 << S.sort_bits;
+    if (nb <= kFuseBlocks) return;
+    const int l = threadIdx.x % kScanDigits, g = threadIdx.x / kScanDigits;
+    for (int d0 = blockIdx.x * kScanDigits; d0 < nd; d0 += gridDim.x * kScanDigits) {
+        int acc = 0;
+        if (d0 + l < nd)
+            for (int b = g; b < nb; b += kScanGroups) acc += S.sort_hist[(long long)b * nd + d0 + l];
+        part[g][l] = acc;
+        __syncthreads();
+        if (g == 0 && d0 + l < nd) {
+            int total = 0;
+            for (int k = 0; k < kScanGroups; ++k) total += part[k][l];
+            S.sort_part[d0 + l] = total;  // copy 0; the other copies stay zero
+        }
+        __syncthreads();
+    }
 }
 
-// row d of hist replaced by its exclusive prefix in the digit-major order: thread t scans its
-// run of k consecutive entries serially, the runs are combined by one block scan
-__global__ void __launch_bounds__(kScanThreads) k_radix_rowscan(SimDev* __restrict__ S, int s, int ipb)
+// Column d of hist replaced by its exclusive prefix over the blocks, from the sum of the totals of the lower
+// digits on: kScanDigits columns per block, whose rows are split into kScanGroups consecutive groups.
+__global__ void __launch_bounds__(kScanThreads) k_radix_rowscan(const SimDev* __restrict__ sims, SortSel sel, int pass)
 {
     __shared__ int wsum[kScanThreads / 64];
-    const int n = S->sp[s].n;
-    const int nb = (n + ipb - 1) / ipb;
-    const int d = blockIdx.x, tid = threadIdx.x;
-    int total;
-    int mine = 0;
-    if (tid < d)
-        for (int k = 0; k < kPartCopies; ++k) mine += S->sort_part[k * kRadix + tid];
-    const int below = block_scan(mine, wsum, &total);
-    (void)below;
-    const int offset = total;  // sum of the totals of digits 0 .. d-1
-    int* row = S->sort_hist + (long long)d * nb;
-    const int k = (nb + kScanThreads - 1) / kScanThreads;
-    const int b0 = min(nb, tid * k), b1 = min(nb, b0 + k);
-    int run = 0;
-    for (int b = b0; b < b1; ++b) run += row[b];
-    const int inc = block_scan(run, wsum, &total);
-    int acc = offset + inc - run;
-    for (int b = b0; b < b1; ++b) {
-        const int x = row[b];
-        row[b] = acc;
-        acc += x;
+    __shared__ int part[kScanGroups][kScanDigits];
+    __shared__ int part8[kScanGroups / 8][kScanDigits];
+    __shared__ int digit[kScanDigits];
+    const SimDev& S = sims[blockIdx.y];
+    const int s = sel_species(S, sel);
+    if (s < 0 || pass >= S.sort_passes) return;
+    const int n = S.sp[s].n, nb = sort_blocks(n, sort_shift(n)), nd = 1 << S.sort_bits;
+    if (nb <= kDirectBlocks) return;
+    const int l = threadIdx.x % kScanDigits, g = threadIdx.x / kScanDigits;
+    const int k = (nb + kScanGroups - 1) / kScanGroups;
+    const int b0 = min(nb, g * k), b1 = min(nb, b0 + k);
+    for (int d0 = blockIdx.x * kScanDigits; d0 < nd; d0 += gridDim.x * kScanDigits) {
+        int lower;  // sum of the totals of digits 0 .. d0 - 1
+        int mine = 0;
+        for (int t = threadIdx.x; t < d0 + kScanDigits && t < nd; t += kScanThreads) {
+            int x = 0;
+            for (int c = 0; c < kPartCopies; ++c) x += S.sort_part[c * kRadixMax + t];
+            if (t < d0) mine += x;
+            else digit[t - d0] = x;
+        }
+        const bool in = d0 + l < nd;
+        int* col = S.sort_hist + d0 + l;
+        int run = 0;
+        int keep[kScanKeep];
+        if (k <= kScanKeep) {
+#pragma unroll
+            for (int t = 0; t < kScanKeep; ++t) {
+                keep[t] = in && b0 + t < b1 ? col[(long long)(b0 + t) * nd] : 0;
+                run += keep[t];
+            }
+        } else if (in) {
+            for (int b = b0; b < b1; ++b) run += col[(long long)b * nd];
+        }
+        part[g][l] = run;
+        block_scan(mine, wsum, &lower);
+        // the groups before: whole eights, then the rest
+        if (g % 8 == 0) {
+            int x = 0;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) x += part[g + t][l];
+            part8[g / 8][l] = x;
+        }
+        __syncthreads();
+        int acc = lower;
+#pragma unroll
+        for (int t = 0; t < kScanDigits; ++t) acc += t < l && d0 + t < nd ? digit[t] : 0;
+#pragma unroll
+        for (int t = 0; t < kScanGroups / 8; ++t) acc += t < g / 8 ? part8[t][l] : 0;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc += t < g % 8 ? part[g / 8 * 8 + t][l] : 0;
+        if (k <= kScanKeep) {
+#pragma unroll
+            for (int t = 0; t < kScanKeep; ++t)
+                if (in && b0 + t < b1) {
+                    col[(long long)(b0 + t) * nd] = acc;
+                    acc += keep[t];
+                }
+        } else if (in) {
+            for (int b = b0; b < b1; ++b) {
+                const int x = col[(long long)b * nd];
+                col[(long long)b * nd] = acc;
+                acc += x;
+            }
+        }
+        __syncthreads();
     }
 }
 
 // Stable scatter of one pass, in rounds of K keys per thread (key j of thread t in a round is the
 // round's key j * kSortBlock + t, so the keys of a round are taken in input order item by item).
 // Each wavefront ranks its lanes' equal digits with ballots and its first lane of each digit
-// stores the count; one thread per digit then turns the (item, wave) counts of its digit, in
-// input order, into the slot of each group's first key, and every key goes to that slot plus its
-// rank.  Four barriers per round: K = 4 for blocks of at least 4096 keys, 1 for smaller ones.
+// stores the count; a thread per item and digit then turns the wavefronts' counts, in input order, into the
+// position of each group's first key in the round, and every key goes to the digit's next slot (base) plus
+// that and its rank.
+constexpr int kScatterCounts = (kSortBlock / 64) * kRadixMax;  // 16-bit counts of a round: 32 KB
 template <int K>
-__global__ void __launch_bounds__(kSortBlock) k_radix_scatter(SimDev* __restrict__ S, int s, int pass, int ipb)
+__device__ __forceinline__ void scatter_block(const SimDev& S, const SpeciesDev& sp, int pass, int n, int ipb, int nb, int b,
+                                              int* base, unsigned short* wcnt, int* jtot, int* wsum)
 {
     constexpr int NW = kSortBlock / 64;
-    __shared__ int running[kRadix];
-    __shared__ int wcnt[K][NW][kRadix];
-    const SpeciesDev& sp = S->sp[s];
+    constexpr int kBits = kDigitBits - (K == 4 ? 2 : K == 2 ? 1 : 0);  // the most a digit has with this K
     const int* kin = (pass & 1) ? sp.keys_alt : sp.keys;
     const int* vin = (pass & 1) ? sp.vals_alt : sp.vals;
     int* kout = (pass & 1) ? sp.keys : sp.keys_alt;
     int* vout = (pass & 1) ? sp.vals : sp.vals_alt;
-    const int n = sp.n;
-    const int nb = (n + ipb - 1) / ipb;
-    const int b = blockIdx.x;
-    if (b >= nb) return;
-    // the digit totals of this pass were consumed by the row scan: clear them for the next pass
-    if (b == 0)
-        for (int d = threadIdx.x; d < kPartCopies * kRadix; d += blockDim.x) S->sort_part[d] = 0;
-    const int shift = pass * kRadixBits;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int d = threadIdx.x; d < kRadix; d += blockDim.x) running[d] = S->sort_hist[d * nb + b];
+    const int bits = S.sort_bits, nd = 1 << bits, shift = pass * bits;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // thread d: the next slot of digit d's keys of this block
+    int run = 0;
+    if (nb > kDirectBlocks) {
+        if (tid < nd) run = S.sort_hist[b * nd + tid];
+    } else {
+        int total = 0, before = 0, all;
+        if (tid < nd)
+            for (int k = 0; k < nb; ++k) {
+                const int x = S.sort_hist[k * nd + tid];
+                total += x;
+                before += k < b ? x : 0;
+            }
+        run = block_scan<kSortBlock>(total, wsum, &all) - total + before;
+    }
+    if (tid < nd) base[tid] = run;
+    const int item = tid >> bits, digit = tid & (nd - 1);  // of the counts
     const int lo = b * ipb, hi = min(n, lo + ipb);
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int base = lo; base < hi; base += K * kSortBlock) {
-        for (int i = threadIdx.x; i < K * NW * kRadix; i += blockDim.x) (&wcnt[0][0][0])[i] = 0;
+    for (int first = lo; first < hi; first += K * kSortBlock) {
+        unsigned* wz = reinterpret_cast<unsigned*>(wcnt);
+        for (int i = tid; i < K * NW * nd / 2; i += kSortBlock) wz[i] = 0u;
         int key[K], val[K], d[K], rank[K];
         bool act[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int i = base + j * kSortBlock + (int)threadIdx.x;
+            const int i = first + j * kSortBlock + tid;
             act[j] = i < hi;
             key[j] = act[j] ? kin[i] : 0;
             val[j] = act[j] ? (pass == 0 ? i : vin[i]) : 0;  // the first pass carries each key's own index
-            d[j] = (key[j] >> shift) & (kRadix - 1);
+            d[j] = (key[j] >> shift) & (nd - 1);
         }
         __syncthreads();
 #pragma unroll
@@ -182,47 +269,106 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_scatter(SimDev* __restrict
             // lanes of this wave holding the same digit
             unsigned long long peers = __ballot(act[j]);
 #pragma unroll
-            for (int bit = 0; bit < kRadixBits; ++bit) {
+            for (int bit = 0; bit < kBits; ++bit) {
                 const unsigned long long m = __ballot(act[j] && ((d[j] >> bit) & 1));
                 peers &= ((d[j] >> bit) & 1) ? m : ~m;
             }
             rank[j] = __popcll(peers & lt);
-            if (act[j] && rank[j] == 0) wcnt[j][wave][d[j]] = __popcll(peers);
+            if (act[j] && rank[j] == 0) wcnt[(j * NW + wave) * nd + d[j]] = (unsigned short)__popcll(peers);
         }
         __syncthreads();
-        for (int dd = threadIdx.x; dd < kRadix; dd += blockDim.x) {
-            int acc = running[dd];
-            for (int j = 0; j < K; ++j)
-                for (int w = 0; w < NW; ++w) {
-                    const int c = wcnt[j][w][dd];
-                    wcnt[j][w][dd] = acc;
-                    acc += c;
-                }
-            running[dd] = acc;
+        int acc = 0;
+        unsigned short* mine = wcnt + (item * NW) * nd + digit;
+        if constexpr (K > 1) {
+            if (item < K) {
+                int total = 0;
+#pragma unroll 4
+                for (int w = 0; w < NW; ++w) total += mine[w * nd];
+                jtot[tid] = total;
+            }
+            __syncthreads();
+            if (item < K)
+                for (int j = 0; j < item; ++j) acc += jtot[(j << bits) + digit];
         }
+        if (item < K)
+            for (int w = 0; w < NW; w += 4) {
+                int c[4];  // (read before the first is replaced: one wait for four)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) c[j] = mine[(w + j) * nd];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    mine[(w + j) * nd] = (unsigned short)acc;
+                    acc += c[j];
+                }
+            }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < K; ++j)
             if (act[j]) {
-                const int off = wcnt[j][wave][d[j]] + rank[j];
+                const int off = base[d[j]] + wcnt[(j * NW + wave) * nd + d[j]] + rank[j];
                 kout[off] = key[j];
                 vout[off] = val[j];
             }
+        __syncthreads();
+        if (item == K - 1) base[digit] += acc;  // (read again after the next round's barriers)
+    }
+}
+
+// K items a thread and round: 4 where the digits' counts of four items fit and the blocks hold as many keys;
+// 1 for a table, whose members' digits differ.
+// At most 64 registers, so that two blocks share a CU.
+template <int K>
+__global__ void __launch_bounds__(kSortBlock, 8) k_radix_scatter(const SimDev* __restrict__ sims, SortSel sel, int pass)
+{
+    __shared__ int base[kRadixMax];
+    __shared__ __align__(4) unsigned short wcnt[kScatterCounts];
+    __shared__ int jtot[K > 1 ? kSortBlock : 1];
+    __shared__ int wsum[kSortBlock / 64];
+    const SimDev& S = sims[blockIdx.y];
+    const int s = sel_species(S, sel);
+    if (s < 0 || pass >= S.sort_passes) return;
+    const SpeciesDev& sp = S.sp[s];
+    const int n = sp.n, sh = sort_shift(n), ipb = 1 << sh, nb = sort_blocks(n, sh);
+    // the digit totals of this pass were consumed by the row scan: clear them for the next pass
+    if (blockIdx.x == 0 && nb > kDirectBlocks)
+        for (int d = threadIdx.x; d < kSortPart; d += kSortBlock) S.sort_part[d] = 0;
+    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+        scatter_block<K>(S, sp, pass, n, ipb, nb, b, base, wcnt, jtot, wsum);
         __syncthreads();
     }
 }
 
 // After the last pass the sorted keys and the source index of each slot sit in keys/vals
-// (even number of passes) or keys_alt/vals_alt (odd).  Gather every particle array into its
-// alternate buffer.
-__global__ void k_permute(SimDev* __restrict__ S, int s, int passes, int elem)
+// (even number of passes) or keys_alt/vals_alt (odd).  The first nr blocks find tile_start[t] = first sorted index
+// whose key >= t * tile volume (lower bound), t = 0..ntiles, the others gather every particle array into
+// its alternate buffer: both need only the sorted keys, and the search's chain of loads (7 us as a launch
+// of its own) hides behind the gather.
+__global__ void k_permute(const SimDev* __restrict__ sims, SortSel sel, int elem, int nr)
 {
-    const SpeciesDev& sp = S->sp[s];
-    const int* perm = (passes & 1) ? sp.vals_alt : sp.vals;
+    const SimDev& S = sims[blockIdx.y];
+    const int s = sel_species(S, sel);
+    if (s < 0) return;
+    const SpeciesDev& sp = S.sp[s];
     const int n = sp.n;
-    const int dims = S->dims;
+    const bool odd = (S.sort_passes & 1) != 0;
+    if ((int)blockIdx.x < nr) {
+        const int* keys = odd ? sp.keys_alt : sp.keys;
+        const int tvol = S.T[0] * S.T[1] * S.T[2];
+        for (int t = blockIdx.x * blockDim.x + threadIdx.x; t <= S.ntiles; t += nr * blockDim.x) {
+            const long long target = (long long)t * tvol;
+            int lo = 0, hi = n;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if ((long long)keys[mid] < target) lo = mid + 1; else hi = mid;
+            }
+            sp.tile_start[t] = lo;
+        }
+        return;
+    }
+    const int* perm = odd ? sp.vals_alt : sp.vals;
+    const int dims = S.dims;
     const bool bound = sp.kind == BOUND;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    for (int i = (blockIdx.x - nr) * blockDim.x + threadIdx.x; i < n; i += (gridDim.x - nr) * blockDim.x) {
         const int j = perm[i];
         sp.cell_alt[i] = sp.cell[j];
         if (elem == 4) {
@@ -249,32 +395,19 @@ __global__ void k_permute(SimDev* __restrict__ S, int s, int passes, int elem)
     }
 }
 
-// tile_start[t] = first sorted index whose key >= t * tile volume (lower bound), t = 0..ntiles.
-// After a sort (swap != 0) the first thread also swaps the particle arrays with their alternates,
-// into which the permutation was gathered; nothing here reads them.
-__global__ void k_tile_ranges(SimDev* __restrict__ S, int s, int passes, int swap)
+// The particle arrays of the sorted species swapped with their alternates, into which the permutation was
+// gathered: mask, a bit per species, or -1 for every moving one that holds particles.
+__device__ __forceinline__ void swap_sorted(SimDev* S, int mask)
 {
-    if (swap && blockIdx.x == 0 && threadIdx.x == 0) {
+    for (int s = 0; s < S->nspecies; ++s) {
         SpeciesDev& w = S->sp[s];
+        if (!(mask < 0 ? w.kind != BOUND && w.n > 0 : (mask >> s) & 1)) continue;
         int* c = w.cell; w.cell = w.cell_alt; w.cell_alt = c;
         for (int a = 0; a < 3; ++a) {
             void* t = w.off[a]; w.off[a] = w.off_alt[a]; w.off_alt[a] = t;
             t = w.v[a]; w.v[a] = w.v_alt[a]; w.v_alt[a] = t;
             t = w.xi[a]; w.xi[a] = w.xi_alt[a]; w.xi_alt[a] = t;
         }
-    }
-    const SpeciesDev& sp = S->sp[s];
-    const int* keys = (passes & 1) ? sp.keys_alt : sp.keys;
-    const int n = sp.n;
-    const int tvol = S->T[0] * S->T[1] * S->T[2];
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t <= S->ntiles; t += gridDim.x * blockDim.x) {
-        const long long target = (long long)t * tvol;
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if ((long long)keys[mid] < target) lo = mid + 1; else hi = mid;
-        }
-        sp.tile_start[t] = lo;
     }
 }
 
@@ -293,14 +426,16 @@ __global__ void k_tile_ranges(SimDev* __restrict__ S, int s, int passes, int swa
 // each block of the first and last taking a contiguous run of rounds: k_compact_count forms each
 // block's totals of active tiles and units, k_compact_scan their exclusive prefix in block order
 // (and whether the lists fit), k_compact_place places the tiles and units of each round with a
-// block scan from its block's prefix.  The block totals and prefixes live in sort_part, which every
-// sort clears at its start.
+// block scan from its block's prefix.  The block totals and prefixes live in compact_part.
+//
+// The launches take a slot of the table per grid.y (an empty slot has no tiles), and the first one also
+// finds the field masks, in the blocks after those of the list.
 constexpr int kCompactK = 4;
-constexpr int kCompactBlocks = kPartCopies * kRadix / 2 - 1;  // block totals in sort_part (its last word: the fit flag)
+constexpr int kCompactBlocks = kCompactPart / 2 - 1;  // block totals in compact_part (its last word: the fit flag)
 
 struct CompactGeom {
     int sh[3], nb[3], vsh, nt, rounds, rpb;
-    __device__ __forceinline__ explicit CompactGeom(const SimDev* S)
+    __device__ __forceinline__ CompactGeom(const SimDev* S, int blocks)
     {
         static_assert((kUnitBlock & (kUnitBlock - 1)) == 0 && kUnitBlock % kCompactK == 0, "blocks of whole thread runs");
         constexpr int kBS = kUnitBlock == 4 ? 2 : (kUnitBlock == 8 ? 3 : 1);  // log2 of kUnitBlock
@@ -311,7 +446,7 @@ struct CompactGeom {
         vsh = sh[0] + sh[1] + sh[2];                 // log2 of the ranks per block
         nt = (nb[0] * nb[1] * nb[2]) << vsh;         // padded ranks
         rounds = (nt + kCompactK * kScanThreads - 1) / (kCompactK * kScanThreads);
-        rpb = (rounds + gridDim.x - 1) / gridDim.x;  // rounds per block
+        rpb = (rounds + blocks - 1) / blocks;        // rounds per block
     }
     // the tiles of ranks r .. r + kCompactK - 1 (-1 beyond the grid); they lie in one block of the
     // list (a block holds a multiple of kCompactK ranks), so its position is divided out once
@@ -348,45 +483,106 @@ __device__ __forceinline__ long long compact_total(const SimDev* S)
     return n;
 }
 // the cap of the list's units: the caller's, or chosen for its active tiles
-__device__ __forceinline__ int compact_cap(const SimDev* S, int active)
+__device__ __forceinline__ int compact_cap(const SimDev* S, long long n, int active)
 {
-    return S->unit_cap > 0 ? S->unit_cap : auto_unit_cap(compact_total(S), active, S->unit_goal);
+    return S->unit_cap > 0 ? S->unit_cap : auto_unit_cap(n, active, S->unit_goal);
 }
-__device__ __forceinline__ int compact_units(int c, int cap) { return (int)(((long long)c + cap - 1) / cap); }
-
-// the k units of tile t (c particles), at slots p .. p + k - 1 of the unit list: equal parts of its
-// species-concatenated order, in whole chunks of 64 where the cap allows
-__device__ __forceinline__ void put_units(SimDev* S, int p, int k, int t, int c, int cap)
+// ceil(c / cap); below 2^22 particles the quotient of the rounded reciprocal is off by at most one
+__device__ __forceinline__ int compact_units(int c, int cap)
 {
-    int per = (c + k - 1) / k;
-    per = (per + 63) / 64 * 64;
-    per = min(per, cap);  // k = ceil(c / cap), so no part is empty
+    if (c >= 1 << 22) return (int)(((unsigned)c - 1u) / (unsigned)cap) + 1;
+    int q = (int)((float)c * __builtin_amdgcn_rcpf((float)cap));
+    int r = c - q * cap;
+    if (r < 0) { --q; r += cap; }
+    if (r >= cap) { ++q; r -= cap; }
+    return q + (r > 0 ? 1 : 0);
+}
+
+// unit q of the k of tile t (c particles): equal parts of its species-concatenated order, in whole chunks of
+// 64 where the cap allows
+__device__ __forceinline__ void put_unit(const SimDev* S, UnitDev& u, int q, int k, int t, int cap)
+{
     const int ns = S->nspecies;
-    int t0[MAXSP], n[MAXSP];
+    int t0[MAXSP], n[MAXSP], c = 0;
 #pragma unroll
     for (int s = 0; s < MAXSP; ++s) {
         t0[s] = s < ns ? S->sp[s].tile_start[t] : 0;
         n[s] = s < ns ? S->sp[s].tile_start[t + 1] - t0[s] : 0;
+        c += n[s];
     }
-    for (int q = 0; q < k; ++q) {
-        UnitDev& u = S->units[p + q];
-        u.tile = t;
-        const int ub = q * per, ue = min(c, (q + 1) * per);
-        int base = 0;  // first index of species s in the concatenated order
+    int per = (c + k - 1) / k;
+    per = (per + 63) / 64 * 64;
+    per = min(per, cap);  // k = ceil(c / cap), so no part is empty
+    u.tile = t;
+    const int ub = q * per, ue = min(c, (q + 1) * per);
+    int base = 0;  // first index of species s in the concatenated order
 #pragma unroll
-        for (int s = 0; s < MAXSP; ++s) {
-            u.range[s][0] = t0[s] + min(max(ub - base, 0), n[s]);
-            u.range[s][1] = t0[s] + min(max(ue - base, 0), n[s]);
-            base += n[s];
-        }
+    for (int s = 0; s < MAXSP; ++s) {
+        u.range[s][0] = t0[s] + min(max(ub - base, 0), n[s]);
+        u.range[s][1] = t0[s] + min(max(ue - base, 0), n[s]);
+        base += n[s];
     }
+}
+
+// fmask of every field task: the columns (x index) of active particle tiles whose deposits reach it, as bits
+// from the first reaching column on; one bit for all of them where there are more than 32 (tiles
+// narrower than 3 cells), and in 1D.  A task reaches one cell past its own along each axis (the last
+// one along an open axis also owns node n).  The active tiles change only with the sort, so the field
+// kernel reads the mask and does not search the tiles itself: its search of up to 150 of them was 2 of
+// the 13 us of the 16^3 cube's field kernel.  One wavefront per task, one candidate tile per lane; block b
+// of nb.
+template <int DIM>
+__device__ __forceinline__ void field_masks(const SimDev& S, int b, int nb)
+{
+    const int lane = threadIdx.x & 63;
+    for (int ft = __builtin_amdgcn_readfirstlane(b * (kScanThreads / 64) + (threadIdx.x >> 6)); ft < S.nftiles;
+         ft += nb * (kScanThreads / 64)) {
+        const int tf[3] = {ft % S.nft[0], (ft / S.nft[0]) % S.nft[1], ft / (S.nft[0] * S.nft[1])};
+        int tlo[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
+        for (int a = 0; a < DIM; ++a) {
+            int x0 = tf[a] * S.FT[a], x1 = x0 + S.FT[a];
+            if (DIM == 3 && a == 1) {
+                // the plane march's row groups end at the last row
+                x0 = max(0, min(x0, S.L[1] - S.FT[1]));
+                x1 = x0 + S.FT[1];
+            }
+            if (DIM == 3 && a == 2 && tf[2] == S.nft[2] - 1) x1 = S.L[2];
+            reaching_tiles(x0, x1, S.T[a], S.Tshift[a], tlo[a], cnt[a]);
+        }
+        unsigned xm = 0u;
+        for (int t = lane; t < cnt[0] * cnt[1] * cnt[2]; t += 64) {
+            int t3[3] = {tlo[0] + t % cnt[0], tlo[1] + (t / cnt[0]) % cnt[1], tlo[2] + t / (cnt[0] * cnt[1])};
+            bool in = true;
+            for (int a = 0; a < DIM; ++a) {
+                if (S.periodic[a]) {
+                    t3[a] %= S.ntile[a];
+                    if (t3[a] < 0) t3[a] += S.ntile[a];
+                } else if (t3[a] < 0 || t3[a] >= S.ntile[a]) {
+                    in = false;
+                }
+            }
+            if (in && compact_count(&S, (t3[2] * S.ntile[1] + t3[1]) * S.ntile[0] + t3[0]) > 0)
+                xm |= DIM > 1 && cnt[0] <= 32 ? 1u << (t % cnt[0]) : ~0u;
+        }
+        for (int off = 32; off > 0; off >>= 1) xm |= (unsigned)__shfl_xor((int)xm, off, 64);
+        if (lane == 0) S.fmask[ft] = xm;
+    }
+}
+
+__device__ __forceinline__ void field_masks(const SimDev& S, int b, int nb)
+{
+    if (S.dims == 1) field_masks<1>(S, b, nb);
+    else if (S.dims == 2) field_masks<2>(S, b, nb);
+    else field_masks<3>(S, b, nb);
 }
 
 // Active tiles per block (sort_hist, free once the species are sorted), where the cap is chosen from
 // their number.
-__global__ void __launch_bounds__(kScanThreads) k_compact_active(SimDev* __restrict__ S)
+__global__ void __launch_bounds__(kScanThreads) k_compact_active(const SimDev* sims)
 {
     __shared__ int wsum[kScanThreads / 64];
+    const SimDev* S = sims + blockIdx.y;
+    if (S->unit_cap > 0 || CompactGeom(S, 1).rounds <= 1) return;
     int ca = 0;
     for (int t = blockIdx.x * kScanThreads + threadIdx.x; t < S->ntiles; t += gridDim.x * kScanThreads)
         ca += compact_count(S, t) > 0 ? 1 : 0;
@@ -395,14 +591,20 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_active(SimDev* __restr
     if (threadIdx.x == 0) S->sort_hist[blockIdx.x] = ta;
 }
 
-__global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restrict__ S, int nactive)
+__global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* sims, int nactive, int nblocks)
 {
     __shared__ int wsum[kScanThreads / 64];
-    const CompactGeom G(S);
+    SimDev* S = sims + blockIdx.y;
+    const CompactGeom G(S, nblocks);
+    if (G.rounds <= 1) return;
+    if ((int)blockIdx.x >= nblocks) {
+        field_masks(*S, blockIdx.x - nblocks, gridDim.x - nblocks);
+        return;
+    }
     int ca = 0, cu = 0;
     int active = 0;
-    if (nactive > 0) block_scan((int)threadIdx.x < nactive ? S->sort_hist[threadIdx.x] : 0, wsum, &active);
-    const int cap = compact_cap(S, active);
+    if (S->unit_cap == 0) block_scan((int)threadIdx.x < nactive ? S->sort_hist[threadIdx.x] : 0, wsum, &active);
+    const int cap = compact_cap(S, compact_total(S), active);
     const int r0 = blockIdx.x * G.rpb, r1 = min(G.rounds, r0 + G.rpb);
     for (int round = r0; round < r1; ++round) {
         int t[kCompactK];
@@ -418,8 +620,8 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restri
     block_scan(ca, wsum, &ta);
     block_scan(cu, wsum, &tu);
     if (threadIdx.x == 0) {
-        S->sort_part[2 * blockIdx.x] = ta;
-        S->sort_part[2 * blockIdx.x + 1] = tu;
+        S->compact_part[2 * blockIdx.x] = ta;
+        S->compact_part[2 * blockIdx.x + 1] = tu;
         if (blockIdx.x == 0) S->unit_now = cap;
     }
 }
@@ -427,21 +629,23 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_count(SimDev* __restri
 // one block: the blocks' exclusive prefixes in place of their totals, the list lengths, and whether
 // the lists fit (a list that does not fit, with particles in tiles the capacity did not count, is
 // dropped whole and flagged: no particle moves this period)
-__global__ void __launch_bounds__(kScanThreads) k_compact_scan(SimDev* __restrict__ S, int nblocks)
+__global__ void __launch_bounds__(kScanThreads) k_compact_scan(SimDev* sims, int nblocks)
 {
     __shared__ int wsum[kScanThreads / 64];
     __shared__ int carry[2];
+    SimDev* S = sims + blockIdx.y;
+    if (CompactGeom(S, 1).rounds <= 1) return;
     if (threadIdx.x < 2) carry[threadIdx.x] = 0;
     __syncthreads();
     for (int base = 0; base < nblocks; base += kScanThreads) {
         const int b = base + threadIdx.x;
-        const int a = b < nblocks ? S->sort_part[2 * b] : 0, u = b < nblocks ? S->sort_part[2 * b + 1] : 0;
+        const int a = b < nblocks ? S->compact_part[2 * b] : 0, u = b < nblocks ? S->compact_part[2 * b + 1] : 0;
         int sa, su;
         const int pa = block_scan(a, wsum, &sa) - a + carry[0];
         const int pu = block_scan(u, wsum, &su) - u + carry[1];
         if (b < nblocks) {
-            S->sort_part[2 * b] = pa;
-            S->sort_part[2 * b + 1] = pu;
+            S->compact_part[2 * b] = pa;
+            S->compact_part[2 * b + 1] = pu;
         }
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -453,21 +657,32 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_scan(SimDev* __restric
     if (threadIdx.x == 0) {
         const int ta = carry[0], tu = carry[1];
         const bool fits = ta <= S->max_slots && tu <= S->max_units;
-        S->sort_part[kPartCopies * kRadix - 1] = fits ? 1 : 0;
+        S->compact_part[kCompactPart - 1] = fits ? 1 : 0;
         *S->n_active = fits ? ta : 0;
         *S->n_units = fits ? tu : 0;
         if (!fits) atomicAdd(S->over_count, 1ull << 40);
     }
 }
 
-// A list of one round (small grids): the three steps in one block and one launch.
-__global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict__ S)
+// A list of one round (small grids): the three steps in block 0, the field masks in the others, in one launch.
+// The tiles' first units sit in LDS once the cap is chosen, so the unit records are written by as many
+// threads as there are units, each finding its tile by bisection (a thread per tile wrote them one after
+// another: 21 us on the 1024^2 disk, now 14, the launch and a chain of loads and scans).
+__global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* sims, int swap)
 {
-    __shared__ int wsum[kScanThreads / 64];
-    const CompactGeom G(S);
+    __shared__ int wsum[2 * (kScanThreads / 64)];
+    __shared__ int s_tile[kCompactK * kScanThreads], s_first[kCompactK * kScanThreads];
+    SimDev* S = sims + blockIdx.y;
+    const CompactGeom G(S, 1);
+    if (G.nt == 0 || G.rounds > 1) return;
+    if (blockIdx.x > 0) {
+        field_masks(*S, blockIdx.x - 1, gridDim.x - 1);
+        return;
+    }
+    const int tid = threadIdx.x;
     int c[kCompactK], tt[kCompactK];
     int ra = 0, ru = 0;
-    G.tiles_of(S, threadIdx.x * kCompactK, tt);
+    G.tiles_of(S, tid * kCompactK, tt);
 #pragma unroll
     for (int j = 0; j < kCompactK; ++j) {
         c[j] = tt[j] >= 0 ? compact_count(S, tt[j]) : 0;
@@ -475,168 +690,115 @@ __global__ void __launch_bounds__(kScanThreads) k_compact_one(SimDev* __restrict
     }
     int ta, tu;
     int pa = block_scan(ra, wsum, &ta) - ra;
-    int cap = compact_cap(S, ta);
+    const long long npart = compact_total(S);
+    int cap = compact_cap(S, npart, ta);
     if (S->unit_cap == 0 && ta > 0 && ta < S->unit_goal) {
         // the bound behind the chosen cap counts a part unit for every tile; the tiles are at hand here, so
         // the smallest cap (in chunks) that keeps to the goal is searched for between N / goal and it
-        int lo = max(unit_floor(compact_total(S)), (int)min((compact_total(S) / S->unit_goal + 64) / 64 * 64, (long long)cap));
+        // (a barrier per try: the wavefronts' counts alternate between two rows)
+        int lo = max(unit_floor(npart), (int)min((npart / S->unit_goal + 64) / 64 * 64, (long long)cap));
+        int row = 0;
         while (lo < cap) {
             const int mid = (lo + (cap - lo) / 2) / 64 * 64;
-            int u = 0, tot;
+            int u = 0;
+            if (__any(ra > 0)) {
 #pragma unroll
-            for (int j = 0; j < kCompactK; ++j) u += compact_units(c[j], mid);
-            block_scan(u, wsum, &tot);
+                for (int j = 0; j < kCompactK; ++j) u += compact_units(c[j], mid);
+                u = seg_scan<int>(u, scan_masks(tid & 63));
+            }
+            if ((tid & 63) == 63) wsum[row * (kScanThreads / 64) + (tid >> 6)] = u;
+            __syncthreads();
+            int tot = 0;
+#pragma unroll
+            for (int w = 0; w < kScanThreads / 64; ++w) tot += wsum[row * (kScanThreads / 64) + w];
             if (tot <= S->unit_goal) cap = mid;
             else lo = mid + 64;
+            row ^= 1;
         }
+        __syncthreads();
     }
 #pragma unroll
     for (int j = 0; j < kCompactK; ++j) ru += compact_units(c[j], cap);
     int pu = block_scan(ru, wsum, &tu) - ru;
     const bool fits = ta <= S->max_slots && tu <= S->max_units;
-#pragma unroll
-    for (int j = 0; j < kCompactK; ++j) {
-        const int t = tt[j];
-        if (t < 0) continue;
-        if (c[j] > 0 && fits) {
-            const int k = compact_units(c[j], cap);
-            S->active[pa] = t;
-            S->tile_slot[t] = pu;
-            S->tile_nslot[t] = k;
-            put_units(S, pu, k, t, c[j], cap);
-            ++pa;
-            pu += k;
-        } else {
-            S->tile_slot[t] = -1;
-            S->tile_nslot[t] = 0;
-        }
-    }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         *S->n_active = fits ? ta : 0;
         *S->n_units = fits ? tu : 0;
         S->unit_now = cap;
         if (!fits) atomicAdd(S->over_count, 1ull << 40);
+        swap_sorted(S, swap);
+    }
+    if (!fits) return;
+#pragma unroll
+    for (int j = 0; j < kCompactK; ++j)
+        if (c[j] > 0) {
+            s_tile[pa] = tt[j];
+            s_first[pa] = pu;
+            ++pa;
+            pu += compact_units(c[j], cap);
+        }
+    __syncthreads();
+    for (int u = tid; u < tu; u += kScanThreads) {
+        int lo = 0, hi = ta;  // the last tile whose first unit is at or before u
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s_first[mid] <= u) lo = mid; else hi = mid;
+        }
+        const int f = s_first[lo], k = (lo + 1 < ta ? s_first[lo + 1] : tu) - f;
+        put_unit(S, S->units[u], u - f, k, s_tile[lo], cap);
     }
 }
 
-__global__ void __launch_bounds__(kScanThreads) k_compact_place(SimDev* __restrict__ S)
+__global__ void __launch_bounds__(kScanThreads) k_compact_place(SimDev* sims, int swap)
 {
     __shared__ int wsum[kScanThreads / 64];
-    const CompactGeom G(S);
+    SimDev* S = sims + blockIdx.y;
+    const CompactGeom G(S, gridDim.x);
+    if (G.rounds <= 1) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) swap_sorted(S, swap);
     const int cap = S->unit_now;
-    const bool fits = S->sort_part[kPartCopies * kRadix - 1] != 0;
-    int oa = S->sort_part[2 * blockIdx.x], ou = S->sort_part[2 * blockIdx.x + 1];  // the blocks before
+    if (S->compact_part[kCompactPart - 1] == 0) return;  // the list does not fit
+    int ou = S->compact_part[2 * blockIdx.x + 1];        // the blocks before
     const int r0 = blockIdx.x * G.rpb, r1 = min(G.rounds, r0 + G.rpb);
     for (int round = r0; round < r1; ++round) {
-        int c[kCompactK], tt[kCompactK];
-        int ra = 0, ru = 0;
+        int k[kCompactK], tt[kCompactK];
+        int ru = 0;
         G.tiles_of(S, round * kCompactK * kScanThreads + threadIdx.x * kCompactK, tt);
 #pragma unroll
-        for (int j = 0; j < kCompactK; ++j) {
-            c[j] = tt[j] >= 0 ? compact_count(S, tt[j]) : 0;
-            ra += c[j] > 0 ? 1 : 0;
-            ru += compact_units(c[j], cap);
-        }
-        int sa, su;
-        int pa = block_scan(ra, wsum, &sa) - ra + oa;
+        for (int j = 0; j < kCompactK; ++j) ru += k[j] = tt[j] >= 0 ? compact_units(compact_count(S, tt[j]), cap) : 0;
+        int su;
         int pu = block_scan(ru, wsum, &su) - ru + ou;
 #pragma unroll
-        for (int j = 0; j < kCompactK; ++j) {
-            const int t = tt[j];
-            if (t < 0) continue;
-            if (c[j] > 0 && fits) {
-                const int k = compact_units(c[j], cap);
-                S->active[pa] = t;
-                S->tile_slot[t] = pu;
-                S->tile_nslot[t] = k;
-                put_units(S, pu, k, t, c[j], cap);
-                ++pa;
-                pu += k;
-            } else {
-                S->tile_slot[t] = -1;
-                S->tile_nslot[t] = 0;
-            }
-        }
-        oa += sa;
+        for (int j = 0; j < kCompactK; ++j)
+            for (int q = 0; q < k[j]; ++q) put_unit(S, S->units[pu++], q, k[j], tt[j], cap);
         ou += su;
     }
 }
 
-// fmask of every field task: the columns (x index) of active particle tiles whose deposits reach it, as bits
-// from the first reaching column on; one bit for all of them where there are more than 32 (tiles
-// narrower than 3 cells), and in 1D.  A task reaches one cell past its own along each axis (the last
-// one along an open axis also owns node n).  The active tiles change only with the sort, so the field
-// kernel reads the mask and does not search the tiles itself: its search of up to 150 of them was 2 of
-// the 13 us of the 16^3 cube's field kernel.  One wavefront per task, one candidate tile per lane.
-template <int DIM>
-__global__ void __launch_bounds__(256) k_field_masks(SimDev* __restrict__ Sd)
-{
-    const SimDev& S = *Sd;
-    const int lane = threadIdx.x & 63;
-    const int ft = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (ft >= S.nftiles) return;
-    const int tf[3] = {ft % S.nft[0], (ft / S.nft[0]) % S.nft[1], ft / (S.nft[0] * S.nft[1])};
-    int tlo[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
-    for (int a = 0; a < DIM; ++a) {
-        int x0 = tf[a] * S.FT[a], x1 = x0 + S.FT[a];
-        if (DIM == 3 && a == 1) {
-            // the plane march's row groups end at the last row
-            x0 = max(0, min(x0, S.L[1] - S.FT[1]));
-            x1 = x0 + S.FT[1];
-        }
-        if (DIM == 3 && a == 2 && tf[2] == S.nft[2] - 1) x1 = S.L[2];
-        reaching_tiles(x0, x1, S.T[a], S.Tshift[a], tlo[a], cnt[a]);
-    }
-    unsigned xm = 0u;
-    for (int t = lane; t < cnt[0] * cnt[1] * cnt[2]; t += 64) {
-        int t3[3] = {tlo[0] + t % cnt[0], tlo[1] + (t / cnt[0]) % cnt[1], tlo[2] + t / (cnt[0] * cnt[1])};
-        bool in = true;
-        for (int a = 0; a < DIM; ++a) {
-            if (S.periodic[a]) {
-                t3[a] %= S.ntile[a];
-                if (t3[a] < 0) t3[a] += S.ntile[a];
-            } else if (t3[a] < 0 || t3[a] >= S.ntile[a]) {
-                in = false;
-            }
-        }
-        if (in && S.tile_slot[(t3[2] * S.ntile[1] + t3[1]) * S.ntile[0] + t3[0]] >= 0)
-            xm |= DIM > 1 && cnt[0] <= 32 ? 1u << (t % cnt[0]) : ~0u;
-    }
-    for (int off = 32; off > 0; off >>= 1) xm |= (unsigned)__shfl_xor((int)xm, off, 64);
-    if (lane == 0) S.fmask[ft] = xm;
-}
-
-static hipError_t enqueue_field_masks(SimDev* dS, const SimDev& h, hipStream_t st)
-{
-    const dim3 grid((h.nftiles + 3) / 4), block(256);
-    switch (h.dims) {
-    case 1: hipLaunchKernelGGL(k_field_masks<1>, grid, block, 0, st, dS); break;
-    case 2: hipLaunchKernelGGL(k_field_masks<2>, grid, block, 0, st, dS); break;
-    default: hipLaunchKernelGGL(k_field_masks<3>, grid, block, 0, st, dS); break;
-    }
-    return hipGetLastError();
-}
-
 // --------------------------------------------------------------------------------------------
-hipError_t enqueue_sort(SimDev* dS, int s, int n, int passes, int elem, hipStream_t st)
+hipError_t enqueue_sort(SimDev* sims, int slots, int s, bool moving, const SortShape& q, hipStream_t st)
 {
-    const int ipb = sort_ipb(n);
-    const int nb = (n + ipb - 1) / ipb;
-    const int g = (n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096;
-    if (n > 0) {
-        hipLaunchKernelGGL(k_keys, dim3(g > 0 ? g : 1), dim3(256), 0, st, dS, s);
-        for (int p = 0; p < passes; ++p) {
-            const int fuse = nb <= kFuseBlocks ? 1 : 0;
-            hipLaunchKernelGGL(k_radix_hist, dim3(nb), dim3(kSortBlock), 0, st, dS, s, p, ipb, fuse);
-            if (!fuse) hipLaunchKernelGGL(k_radix_rowsum, dim3(kRadix), dim3(kScanThreads), 0, st, dS, s, ipb);
-            hipLaunchKernelGGL(k_radix_rowscan, dim3(kRadix), dim3(kScanThreads), 0, st, dS, s, ipb);
-            if (ipb >= 4 * kSortBlock)
-                hipLaunchKernelGGL(k_radix_scatter<4>, dim3(nb), dim3(kSortBlock), 0, st, dS, s, p, ipb);
+    const SortSel sel{s, moving ? 1 : 0};
+    const auto grid = [&](long long blocks) { return dim3((unsigned)std::max(1LL, blocks), slots); };
+    // a table's launches take the blocks of its slots in turns: 512 keep every CU busy
+    const int nb = slots > 1 ? std::min(q.blocks, 512) : q.blocks;
+    const int rows = ((1 << q.bits) + kScanDigits - 1) / kScanDigits;
+    if (q.n > 0)
+        for (int p = 0; p < q.passes; ++p) {
+            if (p == 0) hipLaunchKernelGGL(k_radix_hist<true>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
+            else hipLaunchKernelGGL(k_radix_hist<false>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
+            if (q.blocks > kFuseBlocks) hipLaunchKernelGGL(k_radix_rowsum, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
+            if (q.blocks > kDirectBlocks) hipLaunchKernelGGL(k_radix_rowscan, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
+            if (slots == 1 && q.n > 4 * kSortBlock * 512 && q.bits <= kDigitBits - 2)
+                hipLaunchKernelGGL(k_radix_scatter<4>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
+            else if (slots == 1 && q.n > 2 * kSortBlock * 512 && q.bits <= kDigitBits - 1)
+                hipLaunchKernelGGL(k_radix_scatter<2>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             else
-                hipLaunchKernelGGL(k_radix_scatter<1>, dim3(nb), dim3(kSortBlock), 0, st, dS, s, p, ipb);
+                hipLaunchKernelGGL(k_radix_scatter<1>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
         }
-        hipLaunchKernelGGL(k_permute, dim3(g > 0 ? g : 1), dim3(256), 0, st, dS, s, passes, elem);
-    }
+    const int np = (int)std::min<long long>(((long long)q.n + 255) / 256, slots > 1 ? 1024 : 4096);
+    const int nr = std::min((q.ntiles + 1 + 255) / 256, slots > 1 ? 256 : 4096);
+    hipLaunchKernelGGL(k_permute, grid(np + nr), dim3(256), 0, st, sims, sel, q.elem, nr);
     return hipGetLastError();
 }
 
@@ -647,38 +809,40 @@ hipError_t enqueue_keys_only(SimDev* dS, int s, int n, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t enqueue_ranges(SimDev* dS, int s, int ntiles, int passes, bool swap, hipStream_t st)
+// the rounds of a grid's list (its padded ranks, as CompactGeom counts them)
+static long long compact_rounds(const SimDev& h)
 {
-    const int g = (ntiles + 1 + 255) / 256;
-    hipLaunchKernelGGL(k_tile_ranges, dim3(g), dim3(256), 0, st, dS, s, passes, swap ? 1 : 0);
-    return hipGetLastError();
-}
-
-hipError_t enqueue_compact(SimDev* dS, const SimDev& h, hipStream_t st)
-{
-    // the padded ranks of the list (as CompactGeom counts them) and its rounds, over at most
-    // kCompactBlocks blocks
     long long nt = 1;
     for (int a = 0; a < 3; ++a) {
         const int b = a < h.dims ? kUnitBlock : 1;
         nt *= (long long)((h.ntile[a] + b - 1) / b) * b;
     }
-    const long long rounds = (nt + kCompactK * kScanThreads - 1) / (kCompactK * kScanThreads);
-    if (rounds <= 1) {
-        hipLaunchKernelGGL(k_compact_one, dim3(1), dim3(kScanThreads), 0, st, dS);
-        return enqueue_field_masks(dS, h, st);
+    return (nt + kCompactK * kScanThreads - 1) / (kCompactK * kScanThreads);
+}
+
+void CompactShape::cover(const SimDev& h)
+{
+    const long long r = compact_rounds(h);
+    if (r <= 1) one = true;
+    else {
+        blocks = std::max(blocks, (int)std::min<long long>(r, kCompactBlocks));
+        // (a block per 16384 tiles, within the scratch of the smallest sort, 256 counts)
+        if (h.unit_cap == 0) active = std::max(active, std::min(256, (h.ntiles + 16 * kScanThreads - 1) / (16 * kScanThreads)));
     }
-    const int nb = (int)(rounds < kCompactBlocks ? rounds : kCompactBlocks);
-    // (a block per 16384 tiles, within the scratch of the smallest sort, 256 counts)
-    int na = 0;
-    if (h.unit_cap == 0) {
-        na = std::min(256, (h.ntiles + 16 * kScanThreads - 1) / (16 * kScanThreads));
-        hipLaunchKernelGGL(k_compact_active, dim3(na), dim3(kScanThreads), 0, st, dS);
+    masks = std::max(masks, (h.nftiles + kScanThreads / 64 - 1) / (kScanThreads / 64));
+}
+
+hipError_t enqueue_compact(SimDev* sims, int slots, const CompactShape& q, int swap, hipStream_t st)
+{
+    const int nm = slots > 1 ? std::min(q.masks, 256) : q.masks;
+    if (q.one) hipLaunchKernelGGL(k_compact_one, dim3(1 + nm, slots), dim3(kScanThreads), 0, st, sims, swap);
+    if (q.blocks > 0) {
+        if (q.active > 0) hipLaunchKernelGGL(k_compact_active, dim3(q.active, slots), dim3(kScanThreads), 0, st, sims);
+        hipLaunchKernelGGL(k_compact_count, dim3(q.blocks + nm, slots), dim3(kScanThreads), 0, st, sims, q.active, q.blocks);
+        hipLaunchKernelGGL(k_compact_scan, dim3(1, slots), dim3(kScanThreads), 0, st, sims, q.blocks);
+        hipLaunchKernelGGL(k_compact_place, dim3(q.blocks, slots), dim3(kScanThreads), 0, st, sims, swap);
     }
-    hipLaunchKernelGGL(k_compact_count, dim3(nb), dim3(kScanThreads), 0, st, dS, na);
-    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(kScanThreads), 0, st, dS, nb);
-    hipLaunchKernelGGL(k_compact_place, dim3(nb), dim3(kScanThreads), 0, st, dS);
-    return enqueue_field_masks(dS, h, st);
+    return hipGetLastError();
 }
 
 }  // namespace pic
