@@ -323,13 +323,14 @@ void pic_destroy(pic_sim* s);
 
 /* ---- Batched form: many independent simulations advanced by the same
  * persistent kernels (one launch per phase for the whole batch).  The batch has
- * max_sims fixed slots; one HIP graph per sort period holds the particle and
- * field launches over every slot (an empty slot is passed over), and each
- * member's sorts are a graph of its own, captured when it joins.  Joining and
- * leaving write the member's table entry on the batch stream (the host does not
- * wait); the step graph is captured again only when a joining member needs
- * more than it was captured for (larger LDS windows or block, a kernel
- * variant, or a full-tensor permittivity).  All members share dims, precision
+ * max_sims fixed slots; one HIP graph per sort period holds the sorts and the
+ * particle and field launches over every slot (an empty slot is passed over).
+ * Joining and leaving write the member's table entry on the batch stream (the
+ * host does not wait); the step graph is captured again only when a joining
+ * member needs more than it was captured for (larger LDS windows or block, a
+ * kernel variant, more sorted species, a sort of more than 20-bit cell keys, of
+ * over 4 million particles or of a first one over 32 thousand, a unit list of
+ * over 4096 tiles, or a full-tensor permittivity).  All members share dims, precision
  * and sort period. ---- */
 typedef struct pic_batch pic_batch;
 

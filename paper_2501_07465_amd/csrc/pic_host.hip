@@ -75,7 +75,6 @@ struct pic_sim {
     int batch_refs = 0;      // member of a batch
     SimDev* d_batch = nullptr;  // the member's entry in the batch table
     int bslot = -1;          // its slot
-    hipGraphExec_t bsort = nullptr;  // its periodic sorts in the batch (against its entry)
     pic_batch* owner = nullptr;      // the batch it is in
     int device = 0;          // the GPU current at pic_bind (the arena's and the stream's)
     double einv_max = 1.0;   // largest loaded inverse permittivity (1 for the unit tensor)
@@ -1568,13 +1567,15 @@ extern "C" void pic_destroy(pic_sim* s)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Batched form, over fixed slots.  The step graph (sort_every x (one particle launch + one field
-// launch) over every slot of the table) is captured once; an empty slot holds an entry with no
-// tiles and no units, which the kernels pass over.  A member's sorts are captured into a graph of
-// its own when it joins.  Joining and leaving write one table entry on the batch stream, by a
-// kernel (the host never waits for the device), and the step graph is captured again only when a
+// Batched form, over fixed slots.  The step graph (the sorts, then sort_every x (one particle launch + one
+// field launch), each over every slot of the table) is captured once; an empty slot holds an entry with
+// no tiles and no units, which the kernels pass over.  The sorts of all members share one set of
+// launches: a graph of sorts per member, 12 launches each, was a sixth of a batch of 16 requests (543 us a
+// step, 507 with the shared launches).  Joining and leaving write one table entry on the batch stream,
+// by a kernel (the host never waits for the device), and the step graph is captured again only when a
 // joining member needs more than it was captured for: larger LDS windows or block, a kernel
-// variant, or the full-tensor passes of a member (whose launches the graph holds per slot).
+// variant, more sorted species or passes, another form of the sort's scans or of the unit list, or the
+// full-tensor passes of a member (whose launches the graph holds per slot).
 // ---------------------------------------------------------------------------------------------
 static_assert(sizeof(SimDev) % 4 == 0, "table entries are copied as 32-bit words");
 constexpr size_t kIdleBytes = 256;  // the counters an empty slot's entry points at
@@ -1611,8 +1612,9 @@ struct pic_batch {
     int g_permask = -1;               // the members' common periodic active axes (-1: they differ)
     bool g_eps = false, g_rare = false, g_ext = false;
     std::vector<int> g_tensor;        // slots whose full-tensor passes it launches
-    // sort graphs of members that left, released once the work enqueued before their leaving is done
-    std::vector<std::pair<hipGraphExec_t, hipEvent_t>> retired;
+    int g_moving = 0;                 // species a member has to sort
+    SortShape g_sort;
+    CompactShape g_list;
 };
 
 static int bfail(pic_batch* b, int code, const char* msg)
@@ -1694,20 +1696,22 @@ static void batch_drop_graph(pic_batch* b)
     }
 }
 
-// release the sort graphs of members that left once the device has passed their leaving
-static void batch_reap(pic_batch* b, bool wait)
+// The launches that member s adds to the step graph's sorts: its moving species that hold particles, as the
+// kernels find them in its entry (bound anchors never move), and its unit list.
+static int moving_species(const pic_sim* s)
 {
-    size_t k = 0;
-    for (auto& r : b->retired) {
-        if (wait || hipEventQuery(r.second) == hipSuccess) {
-            if (wait) (void)hipEventSynchronize(r.second);
-            (void)hipGraphExecDestroy(r.first);
-            (void)hipEventDestroy(r.second);
-        } else {
-            b->retired[k++] = r;
-        }
-    }
-    b->retired.resize(k);
+    int k = 0;
+    for (auto& x : s->sp)
+        if (x.d.kind != PIC_BOUND && x.n > 0) ++k;
+    return k;
+}
+
+static void cover_sorts(const pic_sim* s, SortShape& q, CompactShape& c)
+{
+    q.elem = s->es;
+    for (auto& x : s->sp)
+        if (x.d.kind != PIC_BOUND && x.n > 0) q.cover(s->h, (int)x.n);
+    c.cover(s->h);
 }
 
 // does the step graph cover member s (its windows, block, kernel variants, no tensor passes)?
@@ -1717,7 +1721,10 @@ static bool graph_covers(const pic_batch* b, const pic_sim* s)
     const bool tile_ok = b->g_tile[0] == 0 ||
                          (b->g_tile[0] == s->h.T[0] && b->g_tile[1] == s->h.T[1] && b->g_tile[2] == s->h.T[2] &&
                           (b->g_permask < 0 || b->g_permask == sim_permask(s)));
-    return b->gexec && tile_ok && s->h.Vf <= b->g_vf && s->h.Vj <= b->g_vj && s->g.block <= b->g_block &&
+    SortShape q;
+    CompactShape c;
+    cover_sorts(s, q, c);
+    return b->gexec && tile_ok && moving_species(s) <= b->g_moving && b->g_sort.covers(q) && b->g_list.covers(c) && s->h.Vf <= b->g_vf && s->h.Vj <= b->g_vj && s->g.block <= b->g_block &&
            s->field_lds <= b->g_flds && (!s->h.einv || b->g_eps) && (!has_rare(s) || b->g_rare) &&
            (!has_extra(s) || b->g_ext) && !s->h.eoff;
 }
@@ -1746,40 +1753,16 @@ extern "C" int pic_batch_add(pic_batch* b, pic_sim* s)
     if (s->st != b->st) return bfail(b, PIC_EINVAL, "member must be bound to the batch stream");
     int i = 0;
     while (b->slot[i]) ++i;
-    // first sort (bound species) outside the member's sort graph, on its own table
+    // first sort (bound species) outside the step graph, on its own table
     if (s->need_sort || [&] { for (auto& x : s->sp) if (!x.sorted_once) return true; return false; }()) {
         if (enqueue_sort_all(s, nullptr)) return bfail(b, PIC_EDEVICE, s->err.c_str());
     }
     SimDev* entry = b->table + i;
     for (size_t j = 0; j < s->sp.size(); ++j) mirror_species(s, (int)j);
-    const auto undo = [&](const char* msg) {
+    if (retile_fields(s, b->max_sims, b->st) != hipSuccess || put_entry(entry, s->h, b->st) != hipSuccess) {
         (void)retile_fields(s, 1, b->st);
-        return bfail(b, PIC_EDEVICE, msg);
-    };
-    if (retile_fields(s, b->max_sims, b->st) != hipSuccess || put_entry(entry, s->h, b->st) != hipSuccess)
-        return undo("table entry write failed");
-    // the member's periodic sorts, captured against its slot's entry (the host parities are put back:
-    // each launch of the graph flips them)
-    std::vector<int> par, sorted;
-    for (auto& x : s->sp) par.push_back(x.parity);
-    if (hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal) != hipSuccess)
-        return undo("sort capture failed");
-    SimDev* own = s->d;
-    s->d = entry;
-    const int r = enqueue_sort_all(s, &sorted);
-    s->d = own;
-    hipGraph_t graph = nullptr;
-    hipError_t e = hipStreamEndCapture(b->st, &graph);
-    for (size_t j = 0; j < s->sp.size(); ++j) s->sp[j].parity = par[j];
-    hipGraphExec_t gx = nullptr;
-    if (!r && e == hipSuccess) e = hipGraphInstantiate(&gx, graph, nullptr, nullptr, 0);
-    if (graph) (void)hipGraphDestroy(graph);
-    if (r || e != hipSuccess) {
-        (void)put_entry(entry, idle_entry(b), b->st);
-        return undo(r ? s->err.c_str() : hipGetErrorString(e));
+        return bfail(b, PIC_EDEVICE, "table entry write failed");
     }
-    s->bsort = gx;
-    s->graph_species = sorted;
     s->batch_refs = 1;
     s->d_batch = entry;
     s->bslot = i;
@@ -1797,11 +1780,6 @@ extern "C" int pic_batch_remove(pic_batch* b, pic_sim* s)
         return bfail(b, PIC_EINVAL, "not a member");
     const int i = s->bslot;
     if (put_entry(b->table + i, idle_entry(b), b->st) != hipSuccess) return bfail(b, PIC_EDEVICE, "table entry write failed");
-    hipEvent_t ev = nullptr;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess || hipEventRecord(ev, b->st) != hipSuccess)
-        return bfail(b, PIC_EDEVICE, "event failed");
-    b->retired.push_back({s->bsort, ev});
-    s->bsort = nullptr;
     b->slot[i] = nullptr;
     --b->size;
     if (s->h.eoff) batch_drop_graph(b);  // the graph launches this slot's tensor passes
@@ -1814,7 +1792,6 @@ extern "C" int pic_batch_remove(pic_batch* b, pic_sim* s)
     for (size_t j = 0; j < s->sp.size(); ++j) mirror_species(s, (int)j);
     if (retile_fields(s, 1, s->st) != hipSuccess || put_entry(s->d, s->h, s->st) != hipSuccess)
         return bfail(b, PIC_EDEVICE, "table entry write failed");
-    batch_reap(b, false);
     return PIC_OK;
 }
 
@@ -1829,11 +1806,8 @@ extern "C" void pic_batch_destroy(pic_batch* b)
     if (!b) return;
     (void)hipStreamSynchronize(b->st);
     batch_drop_graph(b);
-    batch_reap(b, true);
     for (auto* s : b->slot) {
         if (!s) continue;
-        if (s->bsort) (void)hipGraphExecDestroy(s->bsort);
-        s->bsort = nullptr;
         s->batch_refs = 0;
         s->d_batch = nullptr;
         s->bslot = -1;
@@ -1855,6 +1829,9 @@ static int batch_capture(pic_batch* b)
     b->g_flds = 1;
     b->g_eps = b->g_rare = b->g_ext = false;
     b->g_tensor.clear();
+    b->g_moving = 0;
+    b->g_sort = SortShape();
+    b->g_list = CompactShape();
     bool first = true;
     for (int i = 0; i < b->max_sims; ++i) {
         const pic_sim* s = b->slot[i];
@@ -1874,7 +1851,11 @@ static int batch_capture(pic_batch* b)
         b->g_rare = b->g_rare || has_rare(s);
         b->g_ext = b->g_ext || has_extra(s);
         if (s->h.eoff) b->g_tensor.push_back(i);
+        b->g_moving = std::max(b->g_moving, moving_species(s));
+        cover_sorts(s, b->g_sort, b->g_list);
     }
+    // (grids up to 1024^2 cells have two passes: a batch of smaller ones covers those as well)
+    if (b->g_moving) b->g_sort.passes = std::max(b->g_sort.passes, 2);
     Launch L{};
     L.sims = b->table;
     L.nsims = b->max_sims;
@@ -1895,6 +1876,8 @@ static int batch_capture(pic_batch* b)
     if (hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return bfail(b, PIC_EDEVICE, "capture failed");
     hipError_t e = hipSuccess;
+    for (int j = 0; j < b->g_moving && e == hipSuccess; ++j) e = enqueue_sort(b->table, b->max_sims, j, true, b->g_sort, b->st);
+    if (e == hipSuccess) e = enqueue_compact(b->table, b->max_sims, b->g_list, -1, b->st);
     for (int k = 0; k < b->period && e == hipSuccess; ++k) {
         e = f32 ? Launchers<float>::particles(b->dims, L) : Launchers<double>::particles(b->dims, L);
         // members with a full tensor fold its off-diagonal part into their current first
@@ -1931,15 +1914,13 @@ extern "C" int pic_batch_step(pic_batch* b, int k)
         if (r) return r;
     }
     for (int it = 0; it < k / P; ++it) {
+        if (hipGraphLaunch(b->gexec, b->st) != hipSuccess) return bfail(b, PIC_EDEVICE, "graph launch failed");
         for (auto* s : b->slot) {
             if (!s) continue;
-            if (hipGraphLaunch(s->bsort, b->st) != hipSuccess) return bfail(b, PIC_EDEVICE, "sort graph launch failed");
-            for (int j : s->graph_species) s->sp[j].parity ^= 1;
+            for (auto& x : s->sp)
+                if (x.d.kind != PIC_BOUND && x.n > 0) x.parity ^= 1;
+            s->step += P;
         }
-        if (hipGraphLaunch(b->gexec, b->st) != hipSuccess) return bfail(b, PIC_EDEVICE, "graph launch failed");
-        for (auto* s : b->slot)
-            if (s) s->step += P;
     }
-    batch_reap(b, false);
     return PIC_OK;
 }

@@ -789,9 +789,9 @@ hipError_t enqueue_sort(SimDev* sims, int slots, int s, bool moving, const SortS
             else hipLaunchKernelGGL(k_radix_hist<false>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             if (q.blocks > kFuseBlocks) hipLaunchKernelGGL(k_radix_rowsum, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
             if (q.blocks > kDirectBlocks) hipLaunchKernelGGL(k_radix_rowscan, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
-            if (slots == 1 && q.n > 4 * kSortBlock * 512 && q.bits <= kDigitBits - 2)
+            if (!moving && q.n > 4 * kSortBlock * 512 && q.bits <= kDigitBits - 2)
                 hipLaunchKernelGGL(k_radix_scatter<4>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
-            else if (slots == 1 && q.n > 2 * kSortBlock * 512 && q.bits <= kDigitBits - 1)
+            else if (!moving && q.n > 2 * kSortBlock * 512 && q.bits <= kDigitBits - 1)
                 hipLaunchKernelGGL(k_radix_scatter<2>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             else
                 hipLaunchKernelGGL(k_radix_scatter<1>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);

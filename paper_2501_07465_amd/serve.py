@@ -3,8 +3,8 @@
 Requests (workload dicts with an ``arrival`` time in seconds and a step count) are admitted in
 arrival order while a slot is free and the sum of the admitted simulations' device footprints
 stays within the HBM budget.  Admitted simulations keep their particle and field state resident
-in their own arenas and advance together in one batch of fixed slots: every sort period is the
-members' sort graphs and one captured step graph (per step, one particle launch and one field
+in their own arenas and advance together in one batch of fixed slots: every sort period is one
+captured graph (the members' sorts in shared launches, then per step one particle launch and one field
 launch over all slots).  A request is built on a loading stream of its own (so building it never
 waits for the batch), joins the batch between two periods, and leaves it after its last period:
 its slot is free for the next arrival at once, while its diagnostics are read on a read-back stream

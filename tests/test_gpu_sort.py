@@ -43,3 +43,39 @@ def test_sort_is_stable(n, tile, count):
     x1, _, _ = sim.particles(0)
     # (the positions alone: a particle whose FP32 offset rounds to a whole cell is in the next one after the step)
     assert np.array_equal(x1, x0[order])
+
+
+@pytest.mark.parametrize("slots", [1, 3])
+def test_batch_sorts_match_runs_alone(slots):
+    """The shared sorts of a batch: members of one to three radix passes, one and two moving species, unit
+    lists of one round and of many, joining one after the other, are bit for bit the runs alone."""
+    from paper_2501_07465_amd import pic
+
+    def disk(n, tile, two=False):
+        w = W.small("disk2d")
+        w["n"], w["tile"] = n + [1], tile + [1]
+        for sp in w["species"]:
+            sp["region"]["center"] = [n[0] / 2.0, n[1] / 2.0, 0.0]
+            sp["ppc"] = 30
+        if two:
+            w["species"].append(dict(w["species"][0]))
+        return w
+
+    ws = [disk([64, 60], [16, 8]),            # 12 bits
+          disk([72, 68], [16, 8], two=True),
+          disk([1300, 1100], [4, 4])]         # 21 bits: three passes; 89375 tiles
+    batch = pic.Batch(slots, 2, "fp32")
+    sims = []
+    for w in ws:
+        if len(batch) == slots:
+            batch.remove(batch.members[0])
+        sims.append(pic.Simulation(w, precision="fp32", graphs=False, stream=batch.stream))
+        batch.add(sims[-1])
+        batch.step(40)
+    for i, (w, sim) in enumerate(zip(ws, sims)):
+        print(f"case shared sorts, slots {slots}, member {i}", flush=True)
+        alone = pic.Simulation(w, precision="fp32", graphs=False)
+        alone.step(sim.steps_done)
+        assert all(np.array_equal(a, b) for a, b in zip(sim.fields(), alone.fields()))
+        for k in sim.species:
+            assert all(np.array_equal(a, b) for a, b in zip(sim.particles(k), alone.particles(k)))
