@@ -179,6 +179,11 @@ struct SpeciesDev {
     int* vals_alt;
 };
 
+// DPP steps of the in-cell deposit reduction: deposits are added up within groups of kScanGroup lanes, and
+// each group adds its segment sums to LDS.
+constexpr int kScanSteps = 4;
+constexpr int kScanGroup = 1 << kScanSteps;
+
 // A work unit of the particle kernel: a tile and the unit's range of each species' (sorted) particles.
 struct UnitDev {
     int tile;

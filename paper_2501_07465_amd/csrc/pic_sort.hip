@@ -498,8 +498,11 @@ __device__ __forceinline__ int compact_units(int c, int cap)
     return q + (r > 0 ? 1 : 0);
 }
 
-// unit q of the k of tile t (c particles): equal parts of its species-concatenated order, in whole chunks of
-// 64 where the cap allows
+// unit q of the k of tile t (c particles), a part of its species-concatenated order: the caller's cap at a time,
+// or equal parts, in whole chunks of 64, where the cap is chosen here.  The equal parts are cut between groups
+// of kScanGroup of a species' particles, the groups in which the particle kernel adds up deposits
+// before it rounds them to quanta: the current is then that of the whole tile as one unit, bit for bit,
+// whatever size was chosen (a unit holds at most kScanGroup - 1 particles more than its cap).
 __device__ __forceinline__ void put_unit(const SimDev* S, UnitDev& u, int q, int k, int t, int cap)
 {
     const int ns = S->nspecies;
@@ -510,16 +513,23 @@ __device__ __forceinline__ void put_unit(const SimDev* S, UnitDev& u, int q, int
         n[s] = s < ns ? S->sp[s].tile_start[t + 1] - t0[s] : 0;
         c += n[s];
     }
-    int per = (c + k - 1) / k;
-    per = (per + 63) / 64 * 64;
-    per = min(per, cap);  // k = ceil(c / cap), so no part is empty
+    const bool chosen = S->unit_cap == 0;
+    int per = cap;
+    if (chosen) {
+        per = (c + k - 1) / k;
+        per = min((per + 63) / 64 * 64, cap);  // k = ceil(c / cap), so no part is empty
+    }
     u.tile = t;
     const int ub = q * per, ue = min(c, (q + 1) * per);
     int base = 0;  // first index of species s in the concatenated order
+    auto cut = [&](int at, int s) {
+        const int d = min(max(at - base, 0), n[s]);
+        return t0[s] + (chosen && d < n[s] ? d & ~(kScanGroup - 1) : d);
+    };
 #pragma unroll
     for (int s = 0; s < MAXSP; ++s) {
-        u.range[s][0] = t0[s] + min(max(ub - base, 0), n[s]);
-        u.range[s][1] = t0[s] + min(max(ue - base, 0), n[s]);
+        u.range[s][0] = cut(ub, s);
+        u.range[s][1] = cut(ue, s);
         base += n[s];
     }
 }
