@@ -203,6 +203,7 @@ static int setup_grid(pic_sim* s)
         h.T[a] = g.tile[a];
         h.Tshift[a] = ilog2(g.tile[a]);
         h.ntile[a] = (g.n[a] + g.tile[a] - 1) / g.tile[a];
+        h.tcut[a] = h.periodic[a] ? h.ntile[a] * h.T[a] - g.n[a] : 0;
         if (act && h.periodic[a]) {
             const long long lo_max = (long long)(h.ntile[a] - 1) * h.T[a];
             if (2LL * g.n[a] <= lo_max + h.T[a] + 2)

@@ -194,6 +194,7 @@ struct SimDev {
     int dims, precision, nspecies, ntiles;
     int n_chunks;          // particles of all species, in chunks of 64
     int n[3], L[3], periodic[3], T[3], Tshift[3], ntile[3];
+    int tcut[3];           // cells of the last tile beyond a periodic seam: ntile T - n (0 on open axes)
     int Wf[3], Wj[3];      // particle-window extents (1 on inactive axes)
     int gl[3];             // low halo per axis (kGL on active axes, 0 otherwise)
     int Vf, Vj;            // window volumes
@@ -313,12 +314,18 @@ inline size_t particle_lds_bytes(bool fp64, int vf, int vj, int block)
     return f + 8 * (size_t)(fp64 ? JWords<double>::n : JWords<float>::n) * 3 * (size_t)vj;
 }
 
-// Particle tiles whose deposits reach [x0, x1] along an axis (cells, unwrapped): lo .. lo + count - 1, those
-// tt with tt T - kGL <= x <= tt T + T - 1 + kGHj.
-__host__ __device__ inline void reaching_tiles(int x0, int x1, int T, int sh, int& lo, int& count)
+// Particle tiles whose deposits reach [x0, x1] along axis a (cells, unwrapped, -1 <= x0, x1 <= n on a periodic
+// axis): lo .. lo + count - 1, those tt whose nodes start - kGL .. start + T - 1 + kGHj meet it.  Tile tt starts
+// at tt T; its periodic images are tiles tt + k ntile and start at tt T + k n, which is not (tt + k ntile) T
+// where the last tile is cut short at the seam (by tcut cells): a deposit across the seam is then nearer
+// than the row of whole tiles has it.  The cut tile's windows keep their nominal extent.
+__host__ __device__ inline void reaching_tiles(const SimDev& S, int a, int x0, int x1, int& lo, int& count)
 {
-    lo = -((-(x0 - T + 1 - kGHj)) >> sh);
-    count = ((x1 + kGL) >> sh) - lo + 1;
+    const int T = S.T[a], sh = S.Tshift[a];
+    const int below = kGHj - 1 + S.tcut[a] - x0;  // how far the image of the last tile reaches past x0
+    const int above = x1 + kGL - S.n[a];          // how far x1 reaches into the image of the first tile
+    lo = below >= 0 ? -1 - (below >> sh) : -((-(x0 - T + 1 - kGHj)) >> sh);
+    count = (above >= 0 ? S.ntile[a] + (above >> sh) : (x1 + kGL) >> sh) - lo + 1;
 }
 
 // ---- launchers (defined in the kernel translation units) ---------------------------------------

@@ -557,7 +557,7 @@ __device__ __forceinline__ void field_masks(const SimDev& S, int b, int nb)
                 x1 = x0 + S.FT[1];
             }
             if (DIM == 3 && a == 2 && tf[2] == S.nft[2] - 1) x1 = S.L[2];
-            reaching_tiles(x0, x1, S.T[a], S.Tshift[a], tlo[a], cnt[a]);
+            reaching_tiles(S, a, x0, S.periodic[a] ? min(x1, S.n[a]) : x1, tlo[a], cnt[a]);
         }
         unsigned xm = 0u;
         for (int t = lane; t < cnt[0] * cnt[1] * cnt[2]; t += 64) {
