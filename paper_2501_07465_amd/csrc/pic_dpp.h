@@ -95,7 +95,7 @@ __device__ __forceinline__ void seg_factors(int key, float (&f)[STEPS], bool& ta
 // Segmented inclusive scan of N values at once over the segments of seg_factors: step k adds the value
 // 2^k lanes before times the factor f[k], for every value before step k + 1, so the DPP reads of one
 // value follow the writes of the others and need no wait states.  One fused multiply-add per value and
-// step: v + 1 * t rounds as v + t, v + 0 * t is v (the values are finite).
+// step: v + 1 * t rounds as v + t, v + 0 * t is v for finite values (callers add others by themselves).
 template <int STEPS, int N>
 __device__ __forceinline__ void seg_scan_n(double (&v)[N], const float (&f)[STEPS])
 {
