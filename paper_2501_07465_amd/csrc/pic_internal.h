@@ -66,7 +66,7 @@ constexpr int kPlaneRowsFp64 = 2;
 // 0.360 with 9 (4.1), the FP64 96^3 one 66 us with 2 planes (2.3 rounds) and 51 with 5 (0.96).  Row sweeps
 // of 1, 2, 3, 5 rows: 300^2 9.1, 9.4, 10.5, 12.5 us; 600^2 14.4, 11.3, 11.8, 13.8; 1024^2 25.7, 19.8, 20.0,
 // 18.7; FP64 500^2 17.9, 14.4, 15.0, 16.5.  The members of a batch share the rounds, so a member's tasks are
-// counted once per slot: 16 requests take 622 us a step with 1 row and 564 with 5.
+// counted once per member: 16 requests take 622 us a step with 1 row and 564 with 5.
 constexpr int kFieldWaves = 1024;
 constexpr double kFieldPrologue = 1.5;
 // wavefronts of a SIMD that the field kernel's tasks are rounded by
