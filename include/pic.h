@@ -328,9 +328,9 @@ void pic_destroy(pic_sim* s);
  * Joining and leaving write the member's table entry on the batch stream (the
  * host does not wait); the step graph is captured again only when a joining
  * member needs more than it was captured for (larger LDS windows or block, a
- * kernel variant, more sorted species, a sort of more than 20-bit cell keys, of
- * over 4 million particles or of a first one over 32 thousand, a unit list of
- * over 4096 tiles, or a full-tensor permittivity).  All members share dims, precision
+ * kernel variant, more sorted species, a sort of more than 20-bit cell keys or
+ * the first of over 32 thousand, half a million or 4 million particles, a unit
+ * list of over 4096 tiles, or a full-tensor permittivity).  All members share dims, precision
  * and sort period. ---- */
 typedef struct pic_batch pic_batch;
 

@@ -30,8 +30,10 @@ __host__ __device__ inline int sort_shift(int n)  // log2 of the keys per block
 // Sorts of up to kFuseBlocks blocks form the digit totals in the histogram pass, with one atomic per block
 // and digit met (sort_part is zero on entry: each scatter pass clears it); larger ones in k_radix_rowsum.
 // Up to kDirectBlocks blocks each scatter block scans the histogram itself: its rows are then at most
-// 128 KB in L2, and the launch it saves costs as much as the whole pass (4 to 5 us).
+// 128 KB in L2, and the launch it saves costs as much as the whole pass (4 to 5 us).  Beyond kScanBlocks the
+// scan splits the histogram's columns finer (k_radix_rowscan).
 constexpr int kFuseBlocks = 1024;
+constexpr int kScanBlocks = 512;
 constexpr int kDirectBlocks = 32;
 
 // What a sort's launches are sized for: the most particles, histogram blocks, passes, digit bits and tiles of
@@ -50,7 +52,7 @@ struct SortShape {
     bool covers(const SortShape& q) const
     {
         return passes >= q.passes && (n > 0 || q.n == 0) && (blocks > kDirectBlocks || q.blocks <= kDirectBlocks) &&
-               (blocks > kFuseBlocks || q.blocks <= kFuseBlocks);
+               (blocks > kScanBlocks || q.blocks <= kScanBlocks) && (blocks > kFuseBlocks || q.blocks <= kFuseBlocks);
     }
 };
 

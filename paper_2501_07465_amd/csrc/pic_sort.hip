@@ -112,10 +112,9 @@ __device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
 // Digits of a block of the row scan (64 bytes of each row of hist), and the groups of rows it takes them in.
 constexpr int kScanDigits = 16;
 constexpr int kScanGroups = kScanThreads / kScanDigits;
-constexpr int kScanKeep = 8;  // rows of a group held in registers between its two passes (up to 512 blocks)
-
-// part[d] = sum over blocks b of hist[b * nd + d] (sorts of many blocks: the histogram pass's
-// per-digit atomics would queue on the digits' addresses)
+// Sums over the blocks b of hist[b * nd + d] (sorts of many blocks: the histogram pass's per-digit atomics would
+// queue on the digits' addresses).  The rows are split over kPartCopies blocks, each of which writes a
+// copy of the totals: 16 blocks for all rows of a 256-digit pass took 12.6 us on the 256^3 sphere, now 4.5.
 __global__ void __launch_bounds__(kScanThreads) k_radix_rowsum(const SimDev* __restrict__ sims, SortSel sel, int pass)
 {
     __shared__ int part[kScanGroups][kScanDigits];
@@ -125,59 +124,66 @@ __global__ void __launch_bounds__(kScanThreads) k_radix_rowsum(const SimDev* __r
     const int n = S.sp[s].n, nb = sort_blocks(n, sort_shift(n)), nd = 1 << S.sort_bits;
     if (nb <= kFuseBlocks) return;
     const int l = threadIdx.x % kScanDigits, g = threadIdx.x / kScanDigits;
-    for (int d0 = blockIdx.x * kScanDigits; d0 < nd; d0 += gridDim.x * kScanDigits) {
+    const int copy = blockIdx.x % kPartCopies;
+    for (int d0 = blockIdx.x / kPartCopies * kScanDigits; d0 < nd; d0 += gridDim.x / kPartCopies * kScanDigits) {
         int acc = 0;
         if (d0 + l < nd)
-            for (int b = g; b < nb; b += kScanGroups) acc += S.sort_hist[(long long)b * nd + d0 + l];
+            for (int b = copy * kScanGroups + g; b < nb; b += kPartCopies * kScanGroups) acc += S.sort_hist[(long long)b * nd + d0 + l];
         part[g][l] = acc;
         __syncthreads();
         if (g == 0 && d0 + l < nd) {
             int total = 0;
             for (int k = 0; k < kScanGroups; ++k) total += part[k][l];
-            S.sort_part[d0 + l] = total;  // copy 0; the other copies stay zero
+            S.sort_part[copy * kRadixMax + d0 + l] = total;
         }
         __syncthreads();
     }
 }
 
 // Column d of hist replaced by its exclusive prefix over the blocks, from the sum of the totals of the lower
-// digits on: kScanDigits columns per block, whose rows are split into kScanGroups consecutive groups.
+// digits on: D columns per block, whose rows are split into 1024 / D consecutive groups of at most kScanRows
+// rows each, held in registers between the two passes over them.  D = 16 up to kScanBlocks blocks (64 bytes of a
+// row a block), 4 for up to the 2048 that a sort has: with 16 blocks of 16 columns, the rows read twice, a
+// pass of the 256^3 sphere took 12.8 us, now 8.7 (12.2 where the blocks of a line lie on eight XCDs).
+constexpr int kScanRows = 8;
+static_assert(kScanRows * (kScanThreads / 16) == kScanBlocks && kScanRows * (kScanThreads / 4) == 2048, "rows of a sort's blocks");
+template <int D>
 __global__ void __launch_bounds__(kScanThreads) k_radix_rowscan(const SimDev* __restrict__ sims, SortSel sel, int pass)
 {
+    constexpr int G = kScanThreads / D;
     __shared__ int wsum[kScanThreads / 64];
-    __shared__ int part[kScanGroups][kScanDigits];
-    __shared__ int part8[kScanGroups / 8][kScanDigits];
-    __shared__ int digit[kScanDigits];
+    __shared__ int part[G][D];
+    __shared__ int part8[G / 8][D];
+    __shared__ int digit[D];
     const SimDev& S = sims[blockIdx.y];
     const int s = sel_species(S, sel);
     if (s < 0 || pass >= S.sort_passes) return;
     const int n = S.sp[s].n, nb = sort_blocks(n, sort_shift(n)), nd = 1 << S.sort_bits;
     if (nb <= kDirectBlocks) return;
-    const int l = threadIdx.x % kScanDigits, g = threadIdx.x / kScanDigits;
-    const int k = (nb + kScanGroups - 1) / kScanGroups;
-    const int b0 = min(nb, g * k), b1 = min(nb, b0 + k);
-    for (int d0 = blockIdx.x * kScanDigits; d0 < nd; d0 += gridDim.x * kScanDigits) {
+    const int l = threadIdx.x % D, g = threadIdx.x / D;
+    const int k = (nb + G - 1) / G;
+    const int b0 = min(nb, g * k), rows = min(nb - b0, k);
+    // neighbouring columns on one XCD: the blocks that write parts of a line meet in one L2
+    const int at = gridDim.x % kXcds ? (int)blockIdx.x : (int)(blockIdx.x % kXcds * (gridDim.x / kXcds) + blockIdx.x / kXcds);
+    for (int d0 = at * D; d0 < nd; d0 += gridDim.x * D) {
+        // the rows first: no condition holds these loads back, so all are in flight while the totals are read
+        const bool in = d0 + l < nd && rows > 0;
+        int* col = S.sort_hist + (in ? b0 * nd + d0 + l : 0);
+        int keep[kScanRows];
+#pragma unroll
+        for (int t = 0; t < kScanRows; ++t) keep[t] = col[in ? min(t, rows - 1) * nd : 0];
         int lower;  // sum of the totals of digits 0 .. d0 - 1
         int mine = 0;
-        for (int t = threadIdx.x; t < d0 + kScanDigits && t < nd; t += kScanThreads) {
+        for (int t = threadIdx.x; t < d0 + D && t < nd; t += kScanThreads) {
             int x = 0;
+#pragma unroll
             for (int c = 0; c < kPartCopies; ++c) x += S.sort_part[c * kRadixMax + t];
             if (t < d0) mine += x;
             else digit[t - d0] = x;
         }
-        const bool in = d0 + l < nd;
-        int* col = S.sort_hist + d0 + l;
         int run = 0;
-        int keep[kScanKeep];
-        if (k <= kScanKeep) {
 #pragma unroll
-            for (int t = 0; t < kScanKeep; ++t) {
-                keep[t] = in && b0 + t < b1 ? col[(long long)(b0 + t) * nd] : 0;
-                run += keep[t];
-            }
-        } else if (in) {
-            for (int b = b0; b < b1; ++b) run += col[(long long)b * nd];
-        }
+        for (int t = 0; t < kScanRows; ++t) run += in && t < rows ? keep[t] : 0;
         part[g][l] = run;
         block_scan(mine, wsum, &lower);
         // the groups before: whole eights, then the rest
@@ -190,25 +196,15 @@ __global__ void __launch_bounds__(kScanThreads) k_radix_rowscan(const SimDev* __
         __syncthreads();
         int acc = lower;
 #pragma unroll
-        for (int t = 0; t < kScanDigits; ++t) acc += t < l && d0 + t < nd ? digit[t] : 0;
+        for (int t = 0; t < D; ++t) acc += t < l && d0 + t < nd ? digit[t] : 0;
+        for (int t = 0; t < g / 8; ++t) acc += part8[t][l];
+        for (int t = g / 8 * 8; t < g; ++t) acc += part[t][l];
 #pragma unroll
-        for (int t = 0; t < kScanGroups / 8; ++t) acc += t < g / 8 ? part8[t][l] : 0;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc += t < g % 8 ? part[g / 8 * 8 + t][l] : 0;
-        if (k <= kScanKeep) {
-#pragma unroll
-            for (int t = 0; t < kScanKeep; ++t)
-                if (in && b0 + t < b1) {
-                    col[(long long)(b0 + t) * nd] = acc;
-                    acc += keep[t];
-                }
-        } else if (in) {
-            for (int b = b0; b < b1; ++b) {
-                const int x = col[(long long)b * nd];
-                col[(long long)b * nd] = acc;
-                acc += x;
+        for (int t = 0; t < kScanRows; ++t)
+            if (in && t < rows) {
+                col[t * nd] = acc;
+                acc += keep[t];
             }
-        }
         __syncthreads();
     }
 }
@@ -315,7 +311,8 @@ __device__ __forceinline__ void scatter_block(const SimDev& S, const SpeciesDev&
 }
 
 // K items a thread and round: 4 where the digits' counts of four items fit and the blocks hold as many keys;
-// 1 for a table, whose members' digits differ.
+// 1 for a table, whose members' digits differ (with 4 there where they allow it, two 128^3 spheres of 6.3 million
+// electrons each took 431 us a step for 433).
 // At most 64 registers, so that two blocks share a CU.
 template <int K>
 __global__ void __launch_bounds__(kSortBlock, 8) k_radix_scatter(const SimDev* __restrict__ sims, SortSel sel, int pass)
@@ -797,8 +794,12 @@ hipError_t enqueue_sort(SimDev* sims, int slots, int s, bool moving, const SortS
         for (int p = 0; p < q.passes; ++p) {
             if (p == 0) hipLaunchKernelGGL(k_radix_hist<true>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             else hipLaunchKernelGGL(k_radix_hist<false>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
-            if (q.blocks > kFuseBlocks) hipLaunchKernelGGL(k_radix_rowsum, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
-            if (q.blocks > kDirectBlocks) hipLaunchKernelGGL(k_radix_rowscan, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
+            if (q.blocks > kFuseBlocks)
+                hipLaunchKernelGGL(k_radix_rowsum, grid(rows * kPartCopies), dim3(kScanThreads), 0, st, sims, sel, p);
+            if (q.blocks > kScanBlocks)
+                hipLaunchKernelGGL(k_radix_rowscan<4>, grid(((1 << q.bits) + 3) / 4), dim3(kScanThreads), 0, st, sims, sel, p);
+            else if (q.blocks > kDirectBlocks)
+                hipLaunchKernelGGL(k_radix_rowscan<16>, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
             if (!moving && q.n > 4 * kSortBlock * 512 && q.bits <= kDigitBits - 2)
                 hipLaunchKernelGGL(k_radix_scatter<4>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             else if (!moving && q.n > 2 * kSortBlock * 512 && q.bits <= kDigitBits - 1)
@@ -836,8 +837,9 @@ void CompactShape::cover(const SimDev& h)
     if (r <= 1) one = true;
     else {
         blocks = std::max(blocks, (int)std::min<long long>(r, kCompactBlocks));
-        // (a block per 16384 tiles, within the scratch of the smallest sort, 256 counts)
-        if (h.unit_cap == 0) active = std::max(active, std::min(256, (h.ntiles + 16 * kScanThreads - 1) / (16 * kScanThreads)));
+        // (a round per block within the scratch of the smallest sort, 256 counts; four blocks took 20 us over
+        // the 65536 tiles of the 256^3 sphere, 64 take 5)
+        if (h.unit_cap == 0) active = std::max(active, std::min(256, (h.ntiles + kScanThreads - 1) / kScanThreads));
     }
     masks = std::max(masks, (h.nftiles + kScanThreads / 64 - 1) / (kScanThreads / 64));
 }
