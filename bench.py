@@ -394,7 +394,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--tile", type=str, default=None, help="particle tile, e.g. 16x16 (default: tuned)")
     ap.add_argument("--block", type=int, default=None, help="particle-kernel block (default: tuned)")
-    ap.add_argument("--unit", type=int, default=None, help="particles per work unit (default: tuned; 0 = tile)")
+    ap.add_argument("--unit", type=int, default=None, help="particles per work unit (default: tuned; 0: chosen at each sort)")
     ap.add_argument("--autotune", action="store_true", help="measure the tile/block/unit candidates now")
     ap.add_argument("--eps-inf", type=float, default=3.7,
                     help="background permittivity of the metal for the dielectric legs on the disk (0: skip)")

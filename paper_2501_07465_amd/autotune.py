@@ -2,13 +2,13 @@
 
 The tile sets the LDS window of a particle block (E, B on T + 4 nodes per axis, J on T + 3) and
 the halo overhead; the unit (particles per block) splits a tile's particles over several blocks,
-each with its own current slot, so that a few dense tiles still spread over every compute unit;
+each with its own copy of the windows, so that a few dense tiles still spread over every compute unit;
 the block size sets how many wavefronts share one unit.  The best choice depends on the particle
 density and on how much of the grid the material fills, so it is measured: every candidate that
 fits 64 KiB of LDS is run for a few sort periods through the captured-graph path and scored by
 wall time per step (sort, particle and field kernels together).  The search takes tile x block
-with whole-tile units and with 2048-particle units, then more unit sizes for the best tile and
-block.  Results are cached per workload shape in a JSON file under the user's cache directory.
+with units of the library's choice (0) and of 2048 particles, then more unit sizes for the best tile
+and block.  Results are cached per workload shape in a JSON file under the user's cache directory.
 """
 from __future__ import annotations
 
