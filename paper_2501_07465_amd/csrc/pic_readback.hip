@@ -4,7 +4,7 @@
 // GB/s per thread, where the copy engine delivers about 50.  So chunks are copied into a ring of pinned
 // buffers (a copy into pageable memory is staged through the runtime's own buffers, one piece at a time),
 // and up to kThreads threads convert each chunk while the next ones are in flight.  The fields of the
-// 1024^2 disk (25 MB of floats) take 1.9 ms, those of the 256^3 sphere (407 MB) 16; a pageable
+// 1024^2 disk (25 MB of floats) take 1.6 ms, those of the 256^3 sphere (407 MB) 16; a pageable
 // copy of each array and one converting thread took 4.5 and 147 ms.
 #include "pic_readback.h"
 
@@ -22,10 +22,14 @@ namespace {
 constexpr size_t kSlotBytes = 8u << 20;  // one chunk of all sources of a job
 constexpr int kSlots = 3;
 constexpr int kThreads = 8;
-constexpr size_t kPerThread = 1u << 20;  // bytes copied that are worth a thread of their own
+// Bytes copied that are worth a thread of their own.  A thread takes some 50 us to start: with one per MB, the
+// fields of a 333^2 disk (2.6 MB) took 335 us when read again and again, 261 without threads or ring,
+// 226 with one per 4 MB (25 MB: 1.6 ms either way).
+constexpr size_t kPerThread = 4u << 20;
 constexpr size_t kMaxIdle = 2;           // rings kept for the next exports
-constexpr size_t kSmall = 1u << 20;      // exports up to this size go through pageable memory of their own:
-                                         // a first pinned ring takes longer to allocate than they take
+constexpr size_t kSmall = 3u << 19;      // exports up to this size go through pageable memory of their own:
+                                         // a first pinned ring takes longer to allocate than they take, and
+                                         // 1.2 MB take 160 us so and 171 through the ring, 1.6 MB 196 and 188
 constexpr size_t kMaxSources = 16;
 constexpr size_t kPad = 64;              // sources start on cache lines of their slot
 
