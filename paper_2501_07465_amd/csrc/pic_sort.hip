@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(kScanThreads) k_radix_rowscan(const SimDev* __
     const int s = sel_species(S, sel);
     if (s < 0 || pass >= S.sort_passes) return;
     const int n = S.sp[s].n, nb = sort_blocks(n, sort_shift(n)), nd = 1 << S.sort_bits;
-    if (nb <= kDirectBlocks) return;
+    if (nb <= kDirectBlocks || (nb > kScanBlocks) != (D < 16)) return;
     const int l = threadIdx.x % D, g = threadIdx.x / D;
     const int k = (nb + G - 1) / G;
     const int b0 = min(nb, g * k), rows = min(nb - b0, k);
@@ -796,10 +796,11 @@ hipError_t enqueue_sort(SimDev* sims, int slots, int s, bool moving, const SortS
             else hipLaunchKernelGGL(k_radix_hist<false>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             if (q.blocks > kFuseBlocks)
                 hipLaunchKernelGGL(k_radix_rowsum, grid(rows * kPartCopies), dim3(kScanThreads), 0, st, sims, sel, p);
-            if (q.blocks > kScanBlocks)
-                hipLaunchKernelGGL(k_radix_rowscan<4>, grid(((1 << q.bits) + 3) / 4), dim3(kScanThreads), 0, st, sims, sel, p);
-            else if (q.blocks > kDirectBlocks)
+            // (a table takes both, each for its members: in fours for all of them cost 16 requests 94 us a sort)
+            if (q.blocks > kDirectBlocks && (moving || q.blocks <= kScanBlocks))
                 hipLaunchKernelGGL(k_radix_rowscan<16>, grid(rows), dim3(kScanThreads), 0, st, sims, sel, p);
+            if (q.blocks > kScanBlocks)
+                hipLaunchKernelGGL(k_radix_rowscan<4>, grid(moving ? rows : 4 * rows), dim3(kScanThreads), 0, st, sims, sel, p);
             if (!moving && q.n > 4 * kSortBlock * 512 && q.bits <= kDigitBits - 2)
                 hipLaunchKernelGGL(k_radix_scatter<4>, grid(nb), dim3(kSortBlock), 0, st, sims, sel, p);
             else if (!moving && q.n > 2 * kSortBlock * 512 && q.bits <= kDigitBits - 1)
