@@ -32,7 +32,6 @@ UNITS = {
     "pic_host.hip": [],
     "pic_readback.hip": [],
 }
-DEPS = ["pic_internal.h", "pic_sort.h", "pic_kernels.inc"]
 
 
 def _compile(unit: str, extra: list[str]) -> str:

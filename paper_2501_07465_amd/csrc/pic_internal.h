@@ -95,8 +95,8 @@ inline int field_chunk(long long strips, int n, int most, int waves)
 //     46 us a step with about 950 units, 62 with 1100, 75 with whole tiles; the 64^3 sphere (G = 768) 62,
 //     72 and 67.  U is not below unit_floor: 1024 particles, where a smaller unit gains a few percent for
 //     a simulation on its own (a disk of 227 thousand: 29 us a step with 512, 30 with 1024) but costs a
-//     batch, whose blocks all have work in any case (16 serving requests: 803 us a step with units of 256
-//     and up, 540 to 560 with 1024 to whole tiles); less only where 64 units would not be made (a slab
+//     batch, whose blocks all have work in any case (16 serving requests, each with sorts of its own: 803 us
+//     a step with units of 256 and up, 540 to 560 with 1024 to whole tiles); less only where 64 units would not be made (a slab
 //     of 16 thousand: 18 us with 256, 23 with 1024).
 //   A >= G: units of at most kUnitMax: every block takes several in any case, and smaller ones even
 //     out the last round (a disk of 9 million particles, 1100 active tiles: 187 us a step, 201 with
@@ -207,7 +207,7 @@ struct SimDev {
     void* E[2][3];
     void* B[2][3];
     int* n_active;         // device scalar: tiles that hold particles
-    int max_slots;         // capacity of the active list (tiles that can hold particles)
+    int max_slots;         // most tiles that can hold particles
     UnitDev* units;        // [max_units]
     int* n_units;          // device scalar
     int max_units;         // capacity of the unit list

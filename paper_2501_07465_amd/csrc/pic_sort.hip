@@ -1,5 +1,5 @@
 // pic_sort.hip -- cell sort of libpic: stable LSD radix sort of the int32 tile-major cell keys,
-// permutation of the particle arrays, per-tile particle ranges and the active-tile list.
+// permutation of the particle arrays, per-tile particle ranges and the work units of the tiles that hold particles.
 //
 // Keys and permutation are bit-exact with a stable sort: each pass ranks equal digits in
 // input order (wavefront multisplit with ballots, then waves in order, then blocks in order).
