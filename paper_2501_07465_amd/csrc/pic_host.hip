@@ -1604,6 +1604,7 @@ struct pic_batch {
     std::vector<pic_sim*> slot;       // [max_sims]: the member in each slot, or null
     int size = 0;
     int period = 0;                   // the members' common sort period
+    int share = 1;                    // members that the field tasks are sized for
     int ncu = 256;
     std::string err;
     hipGraphExec_t gexec = nullptr;   // the step graph
@@ -1731,13 +1732,15 @@ static bool graph_covers(const pic_batch* b, const pic_sim* s)
            (!has_extra(s) || b->g_ext) && !s->h.eoff;
 }
 
-// The members that a batch's field tasks are sized for: those present, up to a power of two (so that joining and
-// leaving seldom changes the tasks of the others), at most its slots.  Sized for the slots, present or not,
-// a 64^3 sphere alone in 64 slots took 85.6 us a step, now 66.4, and two of them in 4 slots 94, now 89.
+// The members that a batch's field tasks are sized for: those present, up to a power of two, at most its slots;
+// fewer only when a quarter of them are left (so that joining and leaving seldom changes the tasks of the
+// others).  Sized for the slots, present or not, a 64^3 sphere alone in 64 slots took 85.6 us a step, now
+// 66.4, and two of them in 4 slots 94, now 89.
 static int field_share(const pic_batch* b, int members)
 {
     int share = 1;
     while (share < members) share *= 2;
+    if (share < b->share && members > b->share / 4) share = b->share;
     return std::min(share, b->max_sims);
 }
 
@@ -1925,7 +1928,7 @@ extern "C" int pic_batch_step(pic_batch* b, int k)
     if (b->size == 0) return PIC_OK;
     const int P = b->period;
     if (k % P) return bfail(b, PIC_EINVAL, "k must be a multiple of the sort period");
-    const int share = field_share(b, b->size);
+    const int share = b->share = field_share(b, b->size);
     for (auto* s : b->slot) {
         if (!s || s->fshare == share) continue;
         for (size_t j = 0; j < s->sp.size(); ++j) mirror_species(s, (int)j);
