@@ -50,7 +50,7 @@ def test_runs_give_the_bits_of_runs_alone(kind, members, precision):
 
 @pytest.mark.parametrize("members", [2, 3])
 def test_a_few_sheets_share_the_device(members):
-    """Measured: one sheet 34.5 us a step, two 49, three 56; 62 and 79 with their units one at a time."""
+    """Measured: one sheet 34.5 us a step, two 49, three 61; 62 and 79 with their units one at a time."""
     import torch
     from paper_2501_07465_amd import pic
     batch = pic.Batch(16, 2, "fp32")
